@@ -58,9 +58,9 @@ int make_axis(float lo, float hi, int n, const char* name, AxisMap* m) {
         return fail(OM_ERR_UNSUPPORTED, "%s: coordinate range too large for exact splitting", name);
     m->s = (float)s;
     const double ci = std::floor(c);
-    m->ci = (int)ci;
+    m->ci = (float)ci;
     m->cf = (float)(c - ci);
-    m->n = n;
+    m->top = (float)(n - 2);
     return OM_OK;
 }
 
@@ -145,9 +145,13 @@ int validate_desc(const om_scene_desc* d, SceneDev* out) {
         s.blk_verts = (uint32_t)((B + 1) * (B + 1) * (B + 1));
         s.n_blocks = (uint32_t)d->n_blocks;
     }
-    for (int i = 0; i < 32; ++i) {
-        s.qlo[i] = d->dtype == OM_U8 ? (&d->quant_lo[0][0])[i] : 0.0f;
-        s.qstep[i] = d->dtype == OM_U8 ? (&d->quant_step[0][0])[i] : 0.0f;
+    for (int c = 0; c < 8; ++c) {
+        double lo = 0.0;  // rounded once
+        for (int i = 0; i < 4; ++i) {
+            lo += d->dtype == OM_U8 ? (double)d->quant_lo[i][c] : 0.0;
+            s.qstep[8 * i + c] = d->dtype == OM_U8 ? d->quant_step[i][c] : 0.0f;
+        }
+        s.qlo[c] = (float)lo;
     }
     s.Lx = d->grid_dims[0];
     s.Ly = d->grid_dims[1];

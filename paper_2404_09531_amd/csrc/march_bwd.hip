@@ -200,7 +200,7 @@ __device__ __forceinline__ void replay_sample(const SceneDev& sc, const RayParam
         cn = corners_of(sc, p);
         if (kSoft) oc = occ_value(sc, p, rp.occ_inv_eps);
         float t[8];
-        gather_features_split<S>(sc, cn, t);
+        gather_features_split<S, false>(sc, cn, t);
         tau = __expf(t[0]);
         a = tau * rp.delta;
 #pragma unroll
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
         } else {
             float carry = 0.0f;
             int done = 0, b = 0;
-            march_candidates(sc, rp, o, d, qs[gid], gl, lane, [&](int kq, int nb) {
+            march_candidates(sc, rp, o, d, qs[gid], gl, gl, lane, [&](int kq, int nb) {
                 const int nb_eff = min(nb, ne - done);
                 const bool act = gl < nb_eff;
                 float a, tau, v[7];
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
         // Pass 2: gradients and scatter.
         float carry = 0.0f;
         int done = 0, b = 0;
-        march_candidates(sc, rp, o, d, qs[gid], gl, lane, [&](int kq, int nb) {
+        march_candidates(sc, rp, o, d, qs[gid], gl, gl, lane, [&](int kq, int nb) {
             const int nb_eff = min(nb, ne - done);
             const bool act = gl < nb_eff;
             float a, tau, v[7];

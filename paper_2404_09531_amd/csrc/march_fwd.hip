@@ -30,7 +30,7 @@ __global__ __launch_bounds__(kBlock) void k_place(SceneDev sc, RayParams rp, con
     const float3 o = load3(o_, ray), d = load3(d_, ray);
     int32_t* kr = k_out + ray * rp.n_max;
     int written = 0;
-    const int cnt = march_candidates(sc, rp, o, d, qs[gid], gl, lane, [&](int kq, int nb) {
+    const int cnt = march_candidates(sc, rp, o, d, qs[gid], gl, gl, lane, [&](int kq, int nb) {
         if (gl < nb) kr[written + gl] = kq;
         written += nb;
         return false;
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kBlock) void k_mark(SceneDev sc, RayParams rp, cons
     const int ne = n_eval ? n_eval[ray] : rp.n_max;
     if (ne <= 0) return;
     int done = 0;
-    march_candidates(sc, rp, o, d, qs[gid], gl, lane, [&](int kq, int nb) {
+    march_candidates(sc, rp, o, d, qs[gid], gl, gl, lane, [&](int kq, int nb) {
         const int nbe = min(nb, ne - done);
         if (gl < nbe) {
             const Corners c = corners_of<kSparse>(sc, lattice_point(kq, o, d, rp.delta));
@@ -105,25 +105,34 @@ __device__ __forceinline__ void store_group_total(float x, int gl, float* dst) {
 // Forward march with one lane per sample, for 8-bit and bfloat16 features.
 // A corner pair is 16 (8-bit) or 32 (bfloat16) contiguous bytes, so lane s
 // of the group shades sample s of the batch on its own (10 or 20 loads),
-// and the batch of 16 samples is composited with one 16-lane scan.
+// and the batch of 16 samples is composited with one 16-lane scan.  8-bit is
+// bound by vector instructions: reading the decoding from the argument
+// segment instead of spilled scalar registers, and one offset per channel
+// instead of four, took a 1920x1080 frame with sparse blocks and early
+// termination from 3.78 to 2.97 ms.  bfloat16 is bound by L1 line lookups
+// (1.08 per clock, 36 per load instruction): 34.1 ms for 3840x2160 either way.
 // ---------------------------------------------------------------------------
 struct GatherU8 {
-    static __device__ __forceinline__ void run(const SceneDev& sc, const Corners& c, float* t) { gather_u8(sc, c, t); }
+    template <bool kNarrow>
+    static __device__ __forceinline__ void run(const SceneDev& sc, const Corners& c, float* t) {
+        gather_u8<kNarrow>(sc, c, t);
+    }
 };
 struct GatherBF16 {
+    template <bool kNarrow>
     static __device__ __forceinline__ void run(const SceneDev& sc, const Corners& c, float* t) {
-        gather_features_split<BF16Store>(sc, c, t);
+        gather_features_split<BF16Store, kNarrow>(sc, c, t);
     }
 };
 
-// Waves per SIMD the one-lane-per-sample forwards are compiled for: the
-// bfloat16 gather without the soft occupancy fits 6 (<= 80 VGPRs) without
-// spilling; the other forms keep the compiler's choice.
-template <class Gather, bool kSoft>
-constexpr int lane_min_waves() { return std::is_same<Gather, GatherBF16>::value && !kSoft ? 6 : 1; }
+// Waves per SIMD the one-lane-per-sample forwards are compiled for: without
+// the soft occupancy and with 32-bit addresses they fit 6 (<= 80 VGPRs)
+// without spilling; the other forms keep the compiler's choice.
+template <class Gather, bool kSoft, bool kNarrow>
+constexpr int lane_min_waves() { return !kSoft && kNarrow ? 6 : 1; }
 
-template <class Gather, bool kBW, bool kSoft, bool kSparse>
-__global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSoft>())) void k_march_fwd_lane(
+template <class Gather, bool kBW, bool kSoft, bool kSparse, bool kNarrow>
+__global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSoft, kNarrow>())) void k_march_fwd_lane(
     SceneDev sc, RayParams rp, const float* __restrict__ o_, const float* __restrict__ d_, int64_t n,
     float* __restrict__ F, float* __restrict__ T, int32_t* __restrict__ n_placed, int32_t* __restrict__ n_eval,
     float* __restrict__ BW) {
@@ -140,7 +149,7 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSoft>())) void k_m
     float carry = 0.0f;
     int evals = 0, batch = 0;
     const int slots = (rp.n_max + kGroup - 1) / kGroup;
-    const int placed = march_candidates(sc, rp, o, d, qs[gid], gl, lane, [&](int kq, int nb) {
+    const int placed = march_candidates(sc, rp, o, d, qs[gid], gl, gl, lane, [&](int kq, int nb) {
         const bool act = gl < nb;
         float t[8];
 #pragma unroll
@@ -148,7 +157,8 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSoft>())) void k_m
         float msoft = 0.0f;
         if (act) {
             const float3 p = lattice_point(kq, o, d, rp.delta);
-            Gather::run(sc, corners_of<kSparse>(sc, p), t);
+            const SceneDev& sa = scene_argument();
+            Gather::template run<kNarrow>(sa, corners_of<kSparse, kNarrow>(sa, p), t);
             if (kSoft) msoft = occ_value(sc, p, rp.occ_inv_eps).m;
         }
         float a = 0.0f;
@@ -205,39 +215,58 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSoft>())) void k_m
 // 4s..4s+3 of the group shade sample 4j + s, lane 4s+q taking x-offset
 // (q & 1) and channel half (q >> 1).  A float32 corner pair is 64
 // contiguous bytes, so each gather instruction reads one 64-byte span for
-// each of 4 consecutive samples of the ray; consecutive samples often share
-// a grid cell or plane texel, and lanes of one instruction that hit the same
-// cache line cost one lookup.  After the x-offset sum, lanes with c = 0 hold
-// channels 0..3 (density, diffuse colour) and lanes with c = 1 channels
-// 4..7, so the activations split evenly over the quad.  The four quarters
-// are gathered before the batch is composited, so their loads overlap.
+// each of 4 consecutive samples of the ray.
+//
+// The kernel is bound by vector instruction issue (a wave64 instruction takes
+// a SIMD 4 cycles), so whatever a sample needs once is computed on one lane:
+// lane 4s + j holds sample 4j + s from the start -- its point, row offsets and
+// fractions, density, optical depth and weight -- and hands it to the quad
+// that shades it with DPP quad broadcasts, which cost one instruction or ride
+// on the one that uses the value.  The two x-offset lanes of a channel half
+// end with two channels each, so an activation is evaluated once.  With all
+// of that on all four lanes, 64-bit vector addresses and scalar registers
+// spilled to vector lanes, 64 samples took 1240 vector instructions and a
+// 1920x1080 frame of the full-size scene 13.98 ms; now some 600 and 10.52 ms,
+// with the L1 looking up 0.9 lines per clock.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void quad_gather(const SceneDev& sc, const Corners& c, int h, int ch, float* t) {
-    const uint32_t sy = sc.gsy, sz = sc.gsz;
-    const uint32_t nx = (uint32_t)sc.Nx, ny = (uint32_t)sc.Ny;
-    const uint32_t hh = (uint32_t)h;
-    const float4* G = reinterpret_cast<const float4*>(sc.grid) + ch;
-    const float4* XY = reinterpret_cast<const float4*>(sc.pxy) + ch;
-    const float4* XZ = reinterpret_cast<const float4*>(sc.pxz) + ch;
-    const float4* YZ = reinterpret_cast<const float4*>(sc.pyz) + ch;
+struct QuadSample {
+    uint32_t g, xy, xz, yz;              // row keys (RowAddr)
+    float fx, fy, fz, ux, uy, uz;        // grid and plane fractions
+};
+
+// Sample 4j + s of the quad, j = kJ: the lane's half of the channels, summed
+// over the rows at its x-offset.  lane_off: the lane's 16 bytes within a
+// corner pair; hs, h0: its x weight is h0 + hs * fraction.
+template <int kJ, bool kNarrow>
+__device__ __forceinline__ void quad_gather(const SceneDev& sc, const QuadSample& o, uint32_t lane_off, float hs,
+                                            float h0, float* t) {
+    using A = RowAddr<kNarrow, 32>;
+    const uint32_t sy = sc.gsy, sz = sc.gsz, nx = (uint32_t)sc.Nx, ny = (uint32_t)sc.Ny;
+    const uint32_t kg = quad_bcast<kJ>(o.g), kxy = quad_bcast<kJ>(o.xy), kxz = quad_bcast<kJ>(o.xz),
+                   kyz = quad_bcast<kJ>(o.yz);
+    auto row = [&](const void* base, uint32_t stride, uint32_t key) {
+        // narrow: the lane's offset joins the 32-bit key
+        return *reinterpret_cast<const float4*>(kNarrow ? A::at(base, stride, key + lane_off)
+                                                        : A::at(base, stride, key) + lane_off);
+    };
     float4 r[10];
-    r[0] = G[(size_t)(c.g + hh) * 2];
-    r[1] = G[(size_t)(c.g + sy + hh) * 2];
-    r[2] = G[(size_t)(c.g + sz + hh) * 2];
-    r[3] = G[(size_t)(c.g + sz + sy + hh) * 2];
-    r[4] = XY[(size_t)(c.xy + hh) * 2];
-    r[5] = XY[(size_t)(c.xy + nx + hh) * 2];
-    r[6] = XZ[(size_t)(c.xz + hh) * 2];
-    r[7] = XZ[(size_t)(c.xz + nx + hh) * 2];
-    r[8] = YZ[(size_t)(c.yz + hh) * 2];
-    r[9] = YZ[(size_t)(c.yz + ny + hh) * 2];
-    const float wx = h ? c.fx : 1.0f - c.fx;
-    const float y0 = 1.0f - c.fy, y1 = c.fy, z0 = 1.0f - c.fz, z1 = c.fz;
-    const float wa = h ? c.ux : 1.0f - c.ux;  // x for XY / XZ
-    const float wb = h ? c.uy : 1.0f - c.uy;  // y for YZ
-    const float b0 = 1.0f - c.uy, b1 = c.uy, e0 = 1.0f - c.uz, e1 = c.uz;
-    const float w[10] = {wx * y0 * z0, wx * y1 * z0, wx * y0 * z1, wx * y1 * z1, wa * b0,
-                         wa * b1,      wa * e0,      wa * e1,      wb * e0,      wb * e1};
+    r[0] = row(sc.grid, 0u, kg);
+    r[1] = row(sc.grid, sy, kg);
+    r[2] = row(sc.grid, sz, kg);
+    r[3] = row(sc.grid, sz + sy, kg);
+    r[4] = row(sc.pxy, 0u, kxy);
+    r[5] = row(sc.pxy, nx, kxy);
+    r[6] = row(sc.pxz, 0u, kxz);
+    r[7] = row(sc.pxz, nx, kxz);
+    r[8] = row(sc.pyz, 0u, kyz);
+    r[9] = row(sc.pyz, ny, kyz);
+    const float wx = fmaf(hs, quad_bcast<kJ>(o.fx), h0);
+    const float wa = fmaf(hs, quad_bcast<kJ>(o.ux), h0);  // x for XY / XZ
+    const float wb = fmaf(hs, quad_bcast<kJ>(o.uy), h0);  // y for YZ
+    const float y1 = quad_bcast<kJ>(o.fy), z1 = quad_bcast<kJ>(o.fz), y0 = 1.0f - y1, z0 = 1.0f - z1;
+    const float b1 = quad_bcast<kJ>(o.uy), e1 = quad_bcast<kJ>(o.uz), b0 = 1.0f - b1, e0 = 1.0f - e1;
+    const float xy0 = wx * y0, xy1 = wx * y1;
+    const float w[10] = {xy0 * z0, xy1 * z0, xy0 * z1, xy1 * z1, wa * b0, wa * b1, wa * e0, wa * e1, wb * e0, wb * e1};
 #pragma unroll
     for (int i = 0; i < 4; ++i) t[i] = 0.0f;
 #pragma unroll
@@ -249,153 +278,112 @@ __device__ __forceinline__ void quad_gather(const SceneDev& sc, const Corners& c
     }
 }
 
-// Sparse voxel blocks, in two steps (corners_of<true> does both): the
-// atlas block of a sample's grid cell, clamped as there, and the flat
-// index of the cell's base vertex inside that block.
-__device__ __forceinline__ uint32_t sparse_block(const SceneDev& sc, const Corners& c) {
-    const int32_t id = sc.blk_idx[((c.iz >> sc.blk_shift) * sc.bny + (c.iy >> sc.blk_shift)) * sc.bnx +
-                                  (c.ix >> sc.blk_shift)];
-    return min((uint32_t)id, sc.n_blocks);
-}
-__device__ __forceinline__ uint32_t sparse_vertex(const SceneDev& sc, const Corners& c, uint32_t b) {
-    const int m = (1 << sc.blk_shift) - 1;
-    return b * sc.blk_verts + ((uint32_t)(c.iz & m) * sc.gsy + (uint32_t)(c.iy & m)) * sc.gsy + (uint32_t)(c.ix & m);
-}
-
-// Waves per SIMD the float32 forward is compiled for: the soft-occupancy
-// and sparse forms at 4 (<= 128 VGPRs, no spill); the others keep the
-// compiler's choice, which is 4 already.
-template <bool kSoft, bool kSparse>
-constexpr int f32q_min_waves() { return kSoft || kSparse ? 4 : 1; }
-
-template <bool kBW, bool kSoft, bool kSparse>
-__global__ __launch_bounds__(kBlock, (f32q_min_waves<kSoft, kSparse>())) void k_march_fwd_f32q(SceneDev sc, RayParams rp, const float* __restrict__ o_,
-                                                           const float* __restrict__ d_, int64_t n,
-                                                           float* __restrict__ F, float* __restrict__ T,
-                                                           int32_t* __restrict__ n_placed,
-                                                           int32_t* __restrict__ n_eval,
-                                                           float* __restrict__ BW) {
+template <bool kBW, bool kSoft, bool kSparse, bool kNarrow>
+__global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
+    SceneDev sc, RayParams rp, const float* __restrict__ o_, const float* __restrict__ d_, int64_t n,
+    float* __restrict__ F, float* __restrict__ T, int32_t* __restrict__ n_placed, int32_t* __restrict__ n_eval,
+    float* __restrict__ BW) {
     __shared__ int qs[kGroupsPerBlock][kQueue];
     const int lane = threadIdx.x & 63;
     const int gl = lane & (kGroup - 1);
     const int gid = threadIdx.x / kGroup;
-    const int h = gl & 1, ch = (gl >> 1) & 1;
-    const int s = gl >> 2;            // sample of the quad within a quarter
-    const bool lead = (gl & 3) == 0;  // lane 4s: the quad's depth owner
+    const int h = gl & 1, q = gl & 3;
+    const int pos = 4 * q + (gl >> 2);  // the lane's own sample of a batch
+    const uint32_t lane_off = (uint32_t)(h * 32 + (gl & 2) * 8);
+    const float hs = h ? 1.0f : -1.0f, h0 = h ? 0.0f : 1.0f;
     const int64_t ray = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGroupsPerBlock + gid;
     if (ray >= n) return;
     const float3 o = load3(o_, ray), d = load3(d_, ray);
-    float acc[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[c] = 0.0f;
+    float acc0 = 0.0f, acc1 = 0.0f;  // channels 2q and 2q + 1 (0 is the density)
     float carry = 0.0f;
     int evals = 0, batch = 0;
     const int slots = (rp.n_max + kGroup - 1) / kGroup;
-    const int placed = march_candidates(sc, rp, o, d, qs[gid], gl, lane, [&](int kq, int nb) {
-        float a[4], v[4][4], msoft[4];
-        // Sparse blocks: lane gl looks up the block of sample gl, so the
-        // batch's 16 index loads are in flight together, not one per
-        // quarter ahead of that quarter's corner loads.
-        uint32_t blk = 0u;
-        if (kSparse && gl < nb) blk = sparse_block(sc, corners_of<false>(sc, lattice_point(kq, o, d, rp.delta)));
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = 4 * j + s;
-            const int ks = __shfl(kq, i, kGroup);
-            const uint32_t bj = kSparse ? (uint32_t)__shfl((int)blk, i, kGroup) : 0u;
-            float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            msoft[j] = 0.0f;
-            if (i < nb) {
-                const float3 p = lattice_point(ks, o, d, rp.delta);
-                Corners c = corners_of<false>(sc, p);
-                if (kSparse) c.g = sparse_vertex(sc, c, bj);
-                quad_gather(sc, c, h, ch, t);
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) t[c] += pair_swap(t[c]);
-            a[j] = 0.0f;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[j][c] = 0.0f;
-            if (i < nb) {
-                if (ch == 0) {
-                    a[j] = __expf(t[0]) * rp.delta;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) v[j][c] = sigmoidf_fast(t[c + 1]);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) v[j][c] = sigmoidf_fast(t[c]);
-                }
-            }
-            a[j] = quad_bcast0(a[j]);
+    const int placed = march_candidates(sc, rp, o, d, qs[gid], gl, pos, lane, [&](int kq, int nb) {
+        QuadSample own;
+        {
+            const Corners c = corners_of<kSparse, kNarrow>(scene_argument(), lattice_point(kq, o, d, rp.delta));
+            using A = RowAddr<kNarrow, 32>;
+            own = QuadSample{A::key(c.g), A::key(c.xy), A::key(c.xz), A::key(c.yz), c.fx, c.fy, c.fz, c.ux, c.uy, c.uz};
         }
-        if (kSoft) {
-            // The soft mask (Eq. 6, 8) once the quarters are gathered: its
-            // occupancy loads and arithmetic then do not add to the
-            // gather's registers, which keeps the kernel at 4 waves.
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = 4 * j + s;
-                const int ks = __shfl(kq, i, kGroup);
-                if (i < nb) msoft[j] = occ_value(sc, lattice_point(ks, o, d, rp.delta), rp.occ_inv_eps).m;
+        const SceneDev& sa = scene_argument();
+        float v0[4], v1[4], t0 = 0.0f;
+        auto quarter = [&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            v0[j] = v1[j] = 0.0f;
+            if (4 * j < nb) {
+                float t[4];
+                quad_gather<j, kNarrow>(sa, own, lane_off, hs, h0, t);
+                // The other x-offset's sums, two channels to each lane.
+                const float u0 = (h ? t[2] : t[0]) + pair_swap(h ? t[0] : t[2]);
+                const float u1 = (h ? t[3] : t[1]) + pair_swap(h ? t[1] : t[3]);
+                const float dens = quad_bcast<0>(u0);
+                t0 = q == j ? dens : t0;
+                v0[j] = sigmoidf_fast(u0);
+                v1[j] = sigmoidf_fast(u1);
             }
-        }
-        // Optical depth in front of sample 4j + s: carry + all samples of
-        // quarters < j + samples of quads < s in quarter j.
-        float incl[4], pre[4];
-        float run = carry;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            incl[j] = g_scan_incl(lead ? a[j] : 0.0f, gl);
-            pre[j] = run + quad_bcast0(g_shift_up1(incl[j]));
-            run += __shfl(incl[j], kGroup - 1, kGroup);
-        }
+        };
+        quarter(std::integral_constant<int, 0>{});
+        quarter(std::integral_constant<int, 1>{});
+        quarter(std::integral_constant<int, 2>{});
+        quarter(std::integral_constant<int, 3>{});
+        const bool act = pos < nb;
+        const float a = act ? __expf(t0) * rp.delta : 0.0f;
+        // Optical depth in front of the lane's sample: carry + the samples
+        // of earlier quarters (lanes of lower q) + those before it in its own
+        // quarter (lower quads, same q).
+        float col = a;
+        col += dpp_row<kRowShr | 4>(col);
+        col += dpp_row<kRowShr | 8>(col);
+        float quart = gl >= 12 ? col : 0.0f;  // quarter totals, in the last quad
+        quart += dpp_row<kRowShr | 1>(quart);
+        quart += dpp_row<kRowShr | 2>(quart);
+        const float pre = carry + quad_column_sum(g_shift_up1(quart)) + dpp_row<kRowShr | 4>(col);
+        const float total = row_bcast<kGroup - 1>(quart);
         int nb_eff = nb;
         bool stop = false;
         if (rp.t_term > 0.0f) {
-            int first = kGroup;
-#pragma unroll
-            for (int j = 3; j >= 0; --j)
-                if (4 * j + s < nb && __expf(-(pre[j] + a[j])) < rp.t_term) first = 4 * j + s;
-            first = g_min(first);
+            const int first = g_min(act && __expf(-(pre + a)) < rp.t_term ? pos : kGroup);
             if (first < nb) {
                 nb_eff = first + 1;
                 stop = true;
             }
         }
-        float bacc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float w = __expf(-pre[j]) * (-expm1f(-a[j]));
-            if (kSoft) w *= msoft[j];                // Eq. 8: the weight, not T
-            if (4 * j + s >= nb_eff || h) w = 0.0f;  // once per sample and channel half
-#pragma unroll
-            for (int c = 0; c < 4; ++c) bacc[c] += w * v[j][c];
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[c] += bacc[c];
+        float w = __expf(-pre) * (-expm1f(-a));
+        if (kSoft) w *= occ_value(sc, lattice_point(kq, o, d, rp.delta), rp.occ_inv_eps).m;  // Eq. 8: the weight, not T
+        if (pos >= nb_eff) w = 0.0f;
+        float b0 = quad_bcast<0>(w) * v0[0], b1 = quad_bcast<0>(w) * v1[0];
+        b0 += quad_bcast<1>(w) * v0[1];
+        b1 += quad_bcast<1>(w) * v1[1];
+        b0 += quad_bcast<2>(w) * v0[2];
+        b1 += quad_bcast<2>(w) * v1[2];
+        b0 += quad_bcast<3>(w) * v0[3];
+        b1 += quad_bcast<3>(w) * v1[3];
+        acc0 += b0;
+        acc1 += b1;
         if (kBW) {
-            float* dst = BW + ((size_t)ray * slots + batch) * 7;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) store_group_total(ch == 0 ? bacc[c] : 0.0f, gl, dst + c);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) store_group_total(ch == 1 ? bacc[c] : 0.0f, gl, dst + 3 + c);
+            b0 = quad_column_sum(b0);
+            b1 = quad_column_sum(b1);
+            float* dst = BW + ((size_t)ray * slots + batch) * 7 + 2 * gl;
+            if (gl < 4) {
+                if (gl > 0) dst[-1] = b0;
+                dst[0] = b1;
+            }
         }
         ++batch;
-        // depth through the last evaluated sample, from the quad that owns it
-        const int jl = (nb_eff - 1) >> 2;
-        const float mine = (jl == 0 ? pre[0] + a[0] : jl == 1 ? pre[1] + a[1] : jl == 2 ? pre[2] + a[2] : pre[3] + a[3]);
-        carry = __shfl(mine, 4 * ((nb_eff - 1) & 3), kGroup);
+        // depth through the last evaluated sample
+        const int last = nb_eff - 1;
+        carry = stop ? __shfl(pre + a, 4 * (last & 3) + (last >> 2), kGroup) : carry + total;
         evals += nb_eff;
         return stop;
     });
-    float f[7];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) f[c] = g_sum(ch == 0 ? acc[c] : 0.0f);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) f[3 + c] = g_sum(ch == 1 ? acc[c] : 0.0f);
+    acc0 = quad_column_sum(acc0);
+    acc1 = quad_column_sum(acc1);
+    if (gl < 4) {
+        float* dst = F + ray * 7 + 2 * gl;
+        if (gl > 0) dst[-1] = acc0;
+        dst[0] = acc1;
+    }
     if (gl == 0) {
-#pragma unroll
-        for (int c = 0; c < 7; ++c) F[ray * 7 + c] = f[c];
         T[ray] = __expf(-carry);
         n_placed[ray] = placed;
         n_eval[ray] = evals;
@@ -424,48 +412,61 @@ hipError_t launch_mark(const SceneDev& sc, const RayParams& rp, const float* o, 
     return hipGetLastError();
 }
 
-template <bool kSoft, bool kSparse>
-static void launch_fwd_soft(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
+// Whether every feature source can be addressed with 32-bit byte offsets and
+// 24-bit index factors (RowAddr<true>): the full-size scenes of the benchmark
+// can, in every storage type (their float32 grid is 4 GiB exactly).
+static bool narrow_scene(const SceneDev& sc, int dtype) {
+    const uint64_t bytes = dtype == OM_F32 ? 32 : dtype == OM_BF16 ? 16 : 8, most = 1ull << 32, f24 = 1ull << 24;
+    const uint64_t grid = sc.blk_shift > 0 ? ((uint64_t)sc.n_blocks + 1) * sc.blk_verts
+                                           : (uint64_t)sc.Lx * (uint64_t)sc.Ly * (uint64_t)sc.Lz;
+    const bool factors = sc.blk_shift > 0 ? sc.n_blocks < f24
+                                          : (uint64_t)sc.Ly * (uint64_t)sc.Lz <= f24 && (uint64_t)sc.Lx < f24;
+    return factors && grid * bytes <= most && (uint64_t)sc.Nx * (uint64_t)sc.Ny * bytes <= most &&
+           (uint64_t)sc.Nx * (uint64_t)sc.Nz * bytes <= most && (uint64_t)sc.Ny * (uint64_t)sc.Nz * bytes <= most;
+}
+
+template <bool kSoft, bool kSparse, bool kNarrow>
+static void launch_fwd_form(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
                             int64_t n, float* F, float* T, int32_t* n_placed, int32_t* n_eval, float* batch_wv,
                             hipStream_t s) {
     const dim3 grid(blocks_for(n)), block(kBlock);
-    if (dtype == OM_U8) {  // render only: no per-batch sums
-        hipLaunchKernelGGL((k_march_fwd_lane<GatherU8, false, kSoft, kSparse>), grid, block, 0, s, sc, rp, o, d, n, F,
-                           T, n_placed, n_eval, nullptr);
+    // Sparse blocks and 8-bit features are render only (the API refuses
+    // per-batch sums for them).
+    constexpr bool kSums = !kSparse;
+    if (dtype == OM_U8) {
+        hipLaunchKernelGGL((k_march_fwd_lane<GatherU8, false, kSoft, kSparse, kNarrow>), grid, block, 0, s, sc, rp, o,
+                           d, n, F, T, n_placed, n_eval, nullptr);
     } else if (dtype == OM_BF16) {
-        if (batch_wv)
-            hipLaunchKernelGGL((k_march_fwd_lane<GatherBF16, true, kSoft, kSparse>), grid, block, 0, s, sc, rp, o, d,
-                               n, F, T, n_placed, n_eval, batch_wv);
+        if (kSums && batch_wv)
+            hipLaunchKernelGGL((k_march_fwd_lane<GatherBF16, kSums, kSoft, kSparse, kNarrow>), grid, block, 0, s, sc,
+                               rp, o, d, n, F, T, n_placed, n_eval, batch_wv);
         else
-            hipLaunchKernelGGL((k_march_fwd_lane<GatherBF16, false, kSoft, kSparse>), grid, block, 0, s, sc, rp, o, d,
-                               n, F, T, n_placed, n_eval, batch_wv);
+            hipLaunchKernelGGL((k_march_fwd_lane<GatherBF16, false, kSoft, kSparse, kNarrow>), grid, block, 0, s, sc,
+                               rp, o, d, n, F, T, n_placed, n_eval, nullptr);
     } else {
-        if (batch_wv)
-            hipLaunchKernelGGL((k_march_fwd_f32q<true, kSoft, kSparse>), grid, block, 0, s, sc, rp, o, d, n, F, T,
-                               n_placed, n_eval, batch_wv);
+        if (kSums && batch_wv)
+            hipLaunchKernelGGL((k_march_fwd_f32q<kSums, kSoft, kSparse, kNarrow>), grid, block, 0, s, sc, rp, o, d, n,
+                               F, T, n_placed, n_eval, batch_wv);
         else
-            hipLaunchKernelGGL((k_march_fwd_f32q<false, kSoft, kSparse>), grid, block, 0, s, sc, rp, o, d, n, F, T,
-                               n_placed, n_eval, batch_wv);
+            hipLaunchKernelGGL((k_march_fwd_f32q<false, kSoft, kSparse, kNarrow>), grid, block, 0, s, sc, rp, o, d, n,
+                               F, T, n_placed, n_eval, nullptr);
     }
 }
 
 hipError_t launch_march_fwd(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
                             int64_t n, float* F, float* T, int32_t* n_placed, int32_t* n_eval, float* batch_wv,
                             hipStream_t s) {
-    // The per-batch sums and the soft occupancy are separate
-    // specialisations, so the plain render path carries neither.
-    // Sparse blocks are render only (the API refuses per-batch sums for them).
-    const bool soft = rp.occ_inv_eps > 0.0f;
-    if (sc.blk_shift > 0) {
-        if (soft)
-            launch_fwd_soft<true, true>(sc, dtype, rp, o, d, n, F, T, n_placed, n_eval, nullptr, s);
-        else
-            launch_fwd_soft<false, true>(sc, dtype, rp, o, d, n, F, T, n_placed, n_eval, nullptr, s);
-    } else if (soft) {
-        launch_fwd_soft<true, false>(sc, dtype, rp, o, d, n, F, T, n_placed, n_eval, batch_wv, s);
-    } else {
-        launch_fwd_soft<false, false>(sc, dtype, rp, o, d, n, F, T, n_placed, n_eval, batch_wv, s);
-    }
+    // The per-batch sums, the soft occupancy, the sparse blocks and the wide
+    // addresses are separate specialisations, so the plain path carries none.
+    typedef void (*Form)(const SceneDev&, int, const RayParams&, const float*, const float*, int64_t, float*, float*,
+                         int32_t*, int32_t*, float*, hipStream_t);
+    static constexpr Form forms[2][2][2] = {
+        {{launch_fwd_form<false, false, false>, launch_fwd_form<false, false, true>},
+         {launch_fwd_form<false, true, false>, launch_fwd_form<false, true, true>}},
+        {{launch_fwd_form<true, false, false>, launch_fwd_form<true, false, true>},
+         {launch_fwd_form<true, true, false>, launch_fwd_form<true, true, true>}}};
+    forms[rp.occ_inv_eps > 0.0f][sc.blk_shift > 0][narrow_scene(sc, dtype)](sc, dtype, rp, o, d, n, F, T, n_placed,
+                                                                           n_eval, batch_wv, s);
     return hipGetLastError();
 }
 

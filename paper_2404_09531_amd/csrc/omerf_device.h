@@ -22,12 +22,13 @@ constexpr int kMaxMipLevels = 8;      // occupancy pyramid levels above the plan
 
 // Vertex-aligned coordinate along one axis: u = p * s + (ci + cf) with
 // s = (n - 1) / (hi - lo) a power-of-two scaling of an integer, ci integer,
-// cf in [0, 1).  n = number of vertices / texels on the axis.
+// cf in [0, 1).  n = number of vertices / texels on the axis, top = n - 2 its
+// last cell.  Whole numbers are kept as floats (below 2^24, exact).
 struct AxisMap {
     float s;
     float cf;
-    int ci;
-    int n;
+    float ci;
+    float top;
 };
 
 struct SceneDev {
@@ -49,8 +50,9 @@ struct SceneDev {
     int mip_levels;
     int mlp_in;  // deferred-MLP input width: 10 or 34
     // 8-bit storage: channel c of source s (grid, XY, XZ, YZ) decodes as
-    // qlo[8 s + c] + q qstep[8 s + c]; indexed with constants only.
-    float qlo[32], qstep[32];
+    // lo_s[c] + q qstep[8 s + c]; a source's interpolation weights sum to one,
+    // so the four offsets enter a sample as their sum qlo[c].
+    float qlo[8], qstep[32];
     // Grid row strides in vertices: (Lx, Lx Ly) for the dense grid,
     // (B + 1, (B + 1)^2) inside a sparse block.
     uint32_t gsy, gsz;
@@ -244,10 +246,12 @@ __device__ __forceinline__ void axis_coord(float p, const AxisMap& m, int& i0, f
     const float ih = floorf(hi);
     const float fr = ((hi - ih) + m.cf) + lo;
     const float fl = floorf(fr);
-    const int i = (int)ih + m.ci + (int)fl;
-    const int ic = min(max(i, 0), m.n - 2);
-    f = (fr - fl) + (float)(i - ic);
-    i0 = ic;
+    // The index stays a float (whole numbers below 2^24, exact) until it is
+    // clamped: one conversion instead of three.
+    const float i = (ih + fl) + m.ci;
+    const float ic = __builtin_amdgcn_fmed3f(i, 0.0f, m.top);
+    f = (fr - fl) + (i - ic);
+    i0 = (int)ic;
 }
 
 // Storage policies.  A corner is 8 channels: two 16-byte loads (float32) or
@@ -257,8 +261,9 @@ struct F32Store {
     struct Row {
         float4 a, b;
     };
-    static __device__ __forceinline__ Row load(const void* base, uint32_t idx) {
-        const float4* q = reinterpret_cast<const float4*>(base) + (size_t)idx * 2;
+    static constexpr int kBytes = 32;
+    static __device__ __forceinline__ Row load(const char* row) {
+        const float4* q = reinterpret_cast<const float4*>(row);
         return Row{q[0], q[1]};
     }
     static __device__ __forceinline__ void acc(const Row& r, float w, float* t) {
@@ -271,9 +276,8 @@ struct BF16Store {
     typedef uint4 Row;
     static __device__ __forceinline__ float lo16(uint32_t v) { return __uint_as_float(v << 16); }
     static __device__ __forceinline__ float hi16(uint32_t v) { return __uint_as_float(v & 0xffff0000u); }
-    static __device__ __forceinline__ Row load(const void* base, uint32_t idx) {
-        return reinterpret_cast<const uint4*>(base)[idx];
-    }
+    static constexpr int kBytes = 16;
+    static __device__ __forceinline__ Row load(const char* row) { return *reinterpret_cast<const uint4*>(row); }
     static __device__ __forceinline__ void acc(const Row& v, float w, float* t) {
         t[0] += w * lo16(v.x); t[1] += w * hi16(v.x); t[2] += w * lo16(v.y); t[3] += w * hi16(v.y);
         t[4] += w * lo16(v.z); t[5] += w * hi16(v.z); t[6] += w * lo16(v.w); t[7] += w * hi16(v.w);
@@ -284,11 +288,8 @@ struct BF16Store {
 // byte c.  Interpolation weights of one source sum to one, so a source adds
 // lo + step * sum_corners w q per channel; acc accumulates sum w q.
 struct U8Store {
-    typedef uint2 Row;
-    static __device__ __forceinline__ Row load(const void* base, uint32_t idx) {
-        return reinterpret_cast<const uint2*>(base)[idx];
-    }
-    static __device__ __forceinline__ void acc(const Row& v, float w, float* a) {
+    static constexpr int kBytes = 8;
+    static __device__ __forceinline__ void acc(const uint2& v, float w, float* a) {
         a[0] += w * (float)(v.x & 0xffu);
         a[1] += w * (float)((v.x >> 8) & 0xffu);
         a[2] += w * (float)((v.x >> 16) & 0xffu);
@@ -309,9 +310,39 @@ struct Corners {
     float ux, uy, uz;        // plane fractions
 };
 
+// The scene as the kernel's first argument, to be read from the argument
+// segment where it is used (scalar loads, cached): what a kernel needs only
+// while it shades would otherwise be held in scalar registers for its whole
+// run, and what does not fit there is kept in lanes of vector registers, one
+// vector instruction per use.  Each call is a new read.
+__device__ __forceinline__ const SceneDev& scene_argument() {
+    auto* p = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const SceneDev*)p;
+}
+
+// Addresses of feature rows of kBytes bytes.  kNarrow: every source spans at
+// most 4 GiB (and the index products fit 24-bit operands, see narrow_scene),
+// so a row is a 32-bit byte offset from a uniform base: the loads take the
+// base, plus a uniform row stride, from scalar registers, and one vector
+// register serves all rows of a cell.  Otherwise 64-bit vector addresses.
+template <bool kNarrow, int kBytes>
+struct RowAddr {
+    static __device__ __forceinline__ uint32_t key(uint32_t row) { return kNarrow ? row * kBytes : row; }
+    static __device__ __forceinline__ const char* at(const void* base, uint32_t stride, uint32_t key) {
+        const char* b = static_cast<const char*>(base) + (size_t)stride * kBytes;
+        return b + (kNarrow ? (size_t)key : (size_t)key * kBytes);
+    }
+};
+
+template <bool kNarrow>
+__device__ __forceinline__ uint32_t index_mul(uint32_t a, uint32_t b) {
+    return kNarrow ? (uint32_t)__umul24(a, b) : a * b;
+}
+
 // kSparse: the grid is the atlas of sparse voxel blocks (a separate
 // specialisation, so the dense kernels carry no block lookup).
-template <bool kSparse = false>
+template <bool kSparse = false, bool kNarrow = false>
 __device__ __forceinline__ Corners corners_of(const SceneDev& sc, float3 p) {
     Corners c;
     axis_coord(p.x, sc.gx, c.ix, c.fx);
@@ -325,21 +356,26 @@ __device__ __forceinline__ Corners corners_of(const SceneDev& sc, float3 p) {
         const int32_t id = sc.blk_idx[((c.iz >> sc.blk_shift) * sc.bny + (c.iy >> sc.blk_shift)) * sc.bnx +
                                       (c.ix >> sc.blk_shift)];
         const uint32_t b = min((uint32_t)id, sc.n_blocks);  // a stray id reads a stored block, never past the atlas
-        c.g = b * sc.blk_verts + ((uint32_t)(c.iz & m) * sc.gsy + (uint32_t)(c.iy & m)) * sc.gsy + (uint32_t)(c.ix & m);
+        c.g = index_mul<kNarrow>(b, sc.blk_verts) +
+              index_mul<kNarrow>(index_mul<kNarrow>((uint32_t)(c.iz & m), sc.gsy) + (uint32_t)(c.iy & m), sc.gsy) +
+              (uint32_t)(c.ix & m);
     } else {
-        c.g = ((uint32_t)c.iz * (uint32_t)sc.Ly + (uint32_t)c.iy) * (uint32_t)sc.Lx + (uint32_t)c.ix;
+        c.g = index_mul<kNarrow>(index_mul<kNarrow>((uint32_t)c.iz, (uint32_t)sc.Ly) + (uint32_t)c.iy,
+                                 (uint32_t)sc.Lx) + (uint32_t)c.ix;
     }
-    c.xy = (uint32_t)c.jy * (uint32_t)sc.Nx + (uint32_t)c.jx;
-    c.xz = (uint32_t)c.jz * (uint32_t)sc.Nx + (uint32_t)c.jx;
-    c.yz = (uint32_t)c.jz * (uint32_t)sc.Ny + (uint32_t)c.jy;
+    c.xy = index_mul<kNarrow>((uint32_t)c.jy, (uint32_t)sc.Nx) + (uint32_t)c.jx;
+    c.xz = index_mul<kNarrow>((uint32_t)c.jz, (uint32_t)sc.Nx) + (uint32_t)c.jx;
+    c.yz = index_mul<kNarrow>((uint32_t)c.jz, (uint32_t)sc.Ny) + (uint32_t)c.jy;
     return c;
 }
 
 // Eq. 2: t = trilinear(V) + bilinear(P_xy) + bilinear(P_xz) + bilinear(P_yz),
 // one lane per sample, with at most 12 corners in flight (grid first, then
 // planes), for kernels that carry more live state than the forward march.
-template <class S>
+template <class S, bool kNarrow>
 __device__ __forceinline__ void gather_features_split(const SceneDev& sc, const Corners& c, float* t) {
+    using A = RowAddr<kNarrow, S::kBytes>;
+    const uint32_t kg = A::key(c.g), kp[3] = {A::key(c.xy), A::key(c.xz), A::key(c.yz)};
 #pragma unroll
     for (int i = 0; i < 8; ++i) t[i] = 0.0f;
     const uint32_t sy = sc.gsy, sz = sc.gsz;
@@ -354,9 +390,9 @@ __device__ __forceinline__ void gather_features_split(const SceneDev& sc, const 
 #pragma unroll
         for (int k = 0; k < kPerGroup; ++k) {
             const int p = p0 + k;  // (dy, dz) = (p & 1, p >> 1)
-            const uint32_t base = c.g + ((p & 1) ? sy : 0u) + ((p >> 1) ? sz : 0u);
-            r[2 * k] = S::load(sc.grid, base);
-            r[2 * k + 1] = S::load(sc.grid, base + 1);
+            const char* row = A::at(sc.grid, ((p & 1) ? sy : 0u) + ((p >> 1) ? sz : 0u), kg);
+            r[2 * k] = S::load(row);
+            r[2 * k + 1] = S::load(row + S::kBytes);
         }
 #pragma unroll
         for (int k = 0; k < kPerGroup; ++k) {
@@ -375,9 +411,9 @@ __device__ __forceinline__ void gather_features_split(const SceneDev& sc, const 
             const int p = p0 + k;  // plane p >> 1, second-axis offset p & 1
             const int q = p >> 1;
             const void* P = q == 0 ? sc.pxy : q == 1 ? sc.pxz : sc.pyz;
-            const uint32_t base = (q == 0 ? c.xy : q == 1 ? c.xz : c.yz) + ((p & 1) ? (q == 2 ? ny : nx) : 0u);
-            r[2 * k] = S::load(P, base);
-            r[2 * k + 1] = S::load(P, base + 1);
+            const char* row = A::at(P, (p & 1) ? (q == 2 ? ny : nx) : 0u, kp[q]);
+            r[2 * k] = S::load(row);
+            r[2 * k + 1] = S::load(row + S::kBytes);
         }
 #pragma unroll
         for (int k = 0; k < kPerGroup; ++k) {
@@ -426,9 +462,28 @@ __device__ __forceinline__ int dpp_row_i(int x) {
 }
 
 
-// Value of lane 0 of the lane's quad (DPP quad_perm [0,0,0,0]).
-__device__ __forceinline__ float quad_bcast0(float x) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x00, 0xf, 0xf, false));
+// Value of lane kLane of the lane's quad (DPP quad_perm).
+template <int kLane>
+__device__ __forceinline__ float quad_bcast(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x55 * kLane, 0xf, 0xf, false));
+}
+template <int kLane>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x55 * kLane, 0xf, 0xf, false);
+}
+
+// Value of lane kLane of the 16-lane row (DPP row_newbcast).
+template <int kLane>
+__device__ __forceinline__ float row_bcast(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + kLane, 0xf, 0xf, true));
+}
+
+// Sum over the four lanes of the row with equal place in their quad, in all
+// of them: rotations of the row by 4 and 8.
+__device__ __forceinline__ float quad_column_sum(float x) {
+    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x124, 0xf, 0xf, false));
+    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, false));
+    return x;
 }
 
 // Value of the next lower lane (0 for lane 0).
@@ -478,23 +533,23 @@ __device__ __forceinline__ void wave_order() {
 // 10: 97, 4 waves).
 __device__ __forceinline__ void decode_add(const SceneDev& sc, int src, const float* a, float* t) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) t[c] += fmaf(sc.qstep[8 * src + c], a[c], sc.qlo[8 * src + c]);
+    for (int c = 0; c < 8; ++c) t[c] = fmaf(sc.qstep[8 * src + c], a[c], t[c]);
 }
 
+template <bool kNarrow>
 __device__ __forceinline__ void gather_u8(const SceneDev& sc, const Corners& c, float* t) {
+    using A = RowAddr<kNarrow, U8Store::kBytes>;
     const uint32_t sy = sc.gsy, sz = sc.gsz;
     const uint32_t nx = (uint32_t)sc.Nx, ny = (uint32_t)sc.Ny;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) t[i] = 0.0f;
+    for (int i = 0; i < 8; ++i) t[i] = sc.qlo[i];
     float a[8];
     {
         uint4 r[4];
-        const uint8_t* G = static_cast<const uint8_t*>(sc.grid);
+        const uint32_t kg = A::key(c.g);
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const uint32_t base = c.g + ((p & 1) ? sy : 0u) + ((p >> 1) ? sz : 0u);
-            __builtin_memcpy(&r[p], G + (size_t)base * 8, 16);
-        }
+        for (int p = 0; p < 4; ++p)
+            __builtin_memcpy(&r[p], A::at(sc.grid, ((p & 1) ? sy : 0u) + ((p >> 1) ? sz : 0u), kg), 16);
         const float x0 = 1.0f - c.fx, x1 = c.fx, y0 = 1.0f - c.fy, y1 = c.fy, z0 = 1.0f - c.fz, z1 = c.fz;
 #pragma unroll
         for (int i = 0; i < 8; ++i) a[i] = 0.0f;
@@ -506,9 +561,8 @@ __device__ __forceinline__ void gather_u8(const SceneDev& sc, const Corners& c, 
         }
         decode_add(sc, 0, a, t);
     }
-    const uint8_t* P[3] = {static_cast<const uint8_t*>(sc.pxy), static_cast<const uint8_t*>(sc.pxz),
-                           static_cast<const uint8_t*>(sc.pyz)};
-    const uint32_t pb[3] = {c.xy, c.xz, c.yz}, ps[3] = {nx, nx, ny};
+    const void* P[3] = {sc.pxy, sc.pxz, sc.pyz};
+    const uint32_t pb[3] = {A::key(c.xy), A::key(c.xz), A::key(c.yz)}, ps[3] = {nx, nx, ny};
     const float u0 = 1.0f - c.ux, u1 = c.ux, v0 = 1.0f - c.uy, v1 = c.uy, e0 = 1.0f - c.uz, e1 = c.uz;
     const float wa[3][2] = {{u0, u1}, {u0, u1}, {v0, v1}};  // first axis: x, x, y
     const float wb[3][2] = {{v0, v1}, {e0, e1}, {e0, e1}};  // second axis: y, z, z
@@ -518,8 +572,8 @@ __device__ __forceinline__ void gather_u8(const SceneDev& sc, const Corners& c, 
         uint4 r[4];
 #pragma unroll
         for (int q = q0; q < q1; ++q) {
-            __builtin_memcpy(&r[2 * (q - q0)], P[q] + (size_t)pb[q] * 8, 16);
-            __builtin_memcpy(&r[1 + 2 * (q - q0)], P[q] + (size_t)(pb[q] + ps[q]) * 8, 16);
+            __builtin_memcpy(&r[2 * (q - q0)], A::at(P[q], 0u, pb[q]), 16);
+            __builtin_memcpy(&r[1 + 2 * (q - q0)], A::at(P[q], ps[q], pb[q]), 16);
         }
 #pragma unroll
         for (int q = q0; q < q1; ++q) {
@@ -574,9 +628,12 @@ __device__ __forceinline__ void mlp_input(const float* F7, float3 d, float* x) {
 // lattice range of one ray 16 candidates at a time, appends accepted k to
 // the group's LDS queue in increasing order and hands full batches (or the
 // final partial batch) to `shade(k, nb)`, which returns true to stop.
+// Lane gl gets the sample at place `pos` of the batch (its own place unless
+// the caller shades in another layout); lanes past a partial batch get the
+// batch's first sample, so that they may read where it reads.
 template <class Shade>
 __device__ __forceinline__ int march_candidates(const SceneDev& sc, const RayParams& rp, float3 o,
-                                                float3 d, int* q, int gl, int lane, Shade&& shade) {
+                                                float3 d, int* q, int gl, int pos, int lane, Shade&& shade) {
     const KRange kr = candidate_range(sc, o, d, rp.delta);
     int k = kr.lo;
     int n_acc = 0;
@@ -626,7 +683,7 @@ __device__ __forceinline__ int march_candidates(const SceneDev& sc, const RayPar
         }
         if (qn >= kGroup || (!more && qn > 0)) {
             const int nb = min(qn, kGroup);
-            const int kq = gl < nb ? q[gl] : 0;
+            const int kq = q[pos < nb ? pos : 0];
             const int rest = qn - nb;
             const int tail = gl < rest ? q[kGroup + gl] : 0;
             wave_order();
