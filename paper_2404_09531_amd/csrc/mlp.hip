@@ -379,12 +379,14 @@ template <int NIN>
 static void launch_mlp_bwd_nin(const float* W, const RayParams& rp, const float* F, const float* d,
                                const int32_t* n_eval, const float* dC, const float* dF, int64_t n, float* G8,
                                float* gmlp, hipStream_t s) {
-    // At least 8 quads per wave; at most 512 blocks, whose LDS sums then
-    // cost at most 512 global atomics per MLP parameter.
+    // At most 512 blocks, whose LDS sums then cost at most 512 global atomics
+    // per MLP parameter, and at least a quad per wave: a wave's quads are a
+    // serial chain, so small batches spread over the chip (4,096 rays at 8
+    // quads per wave ran in 8 blocks, 32.6 us).
     const int64_t nq = (n + 3) / 4;
     const int64_t waves = mlp_bwd_block<NIN>() / 64;
     int64_t qpb = (nq + 511) / 512;
-    if (qpb < 8 * waves) qpb = 8 * waves;
+    if (qpb < waves) qpb = waves;
     qpb = (qpb + waves - 1) / waves * waves;
     const int64_t nb = (nq + qpb - 1) / qpb;
     hipLaunchKernelGGL(k_mlp_bwd<NIN>, dim3((unsigned)nb), dim3(mlp_bwd_block<NIN>()), 0, s, W, rp, F, d, n_eval, dC,
@@ -404,40 +406,104 @@ hipError_t launch_mlp_bwd(const float* W, int mlp_in, const RayParams& rp, const
 
 // ---------------------------------------------------------------------------
 // L2 loss and its gradient.  dL/dC is elementwise float32 over the whole
-// grid.  The loss value is summed by ONE workgroup in a fixed order -- each
-// lane a fixed strided subset, then a fixed butterfly over the wave and a
-// fixed sum over the waves -- so two calls on the same colours return the
-// same bits (a cross-block atomic sum would not).  It is accumulated in
-// float64 only for the finite-difference checks (om_l2_loss_fp64) and in
-// float32 for the optional loss of a training step.
+// grid.  The loss value is summed in a fixed order that depends on n alone --
+// each lane a fixed strided subset, then a fixed butterfly over the wave and a
+// fixed sum over the waves and blocks -- so two calls on the same colours
+// return the same bits (an atomic sum would not).  It is accumulated in
+// float64 only for the finite-difference checks (om_l2_loss_fp64, one
+// workgroup) and in float32 for the optional loss of a training step.
+//
+// The training step's loss: up to kLossOneBlock values in one workgroup that
+// also writes the gradient (one launch).  Above, one workgroup is bound by the
+// latency of its few loads in flight (786,432 values took 228 us, 3.1 M 897),
+// so a first launch leaves one partial sum per block in the gradient buffer,
+// whose first kLossParts entries are then read as such by the block that
+// overwrites them in the second: 11 and 14 us together with the gradient.
 // ---------------------------------------------------------------------------
 constexpr int kLossBlock = 1024;
+constexpr int kLossParts = kBlock;
+constexpr int64_t kLossOneBlock = 32768;
 
+// Block sum in a fixed order; the result is valid in thread 0.
+template <class Acc, int kThreads>
+__device__ __forceinline__ Acc block_sum(Acc s, Acc* part) {
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    Acc t = 0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < kThreads / 64; ++w) t += part[w];
+    return t;
+}
+
+// Sum over this thread's strided subset of m terms, eight in flight.
+template <class Acc, class Term>
+__device__ __forceinline__ Acc strided_sum(int64_t first, int64_t stride, int64_t m, Term&& term) {
+    Acc s[8] = {};
+    int64_t i = first;
+    for (; i + 7 * stride < m; i += 8 * stride) {
+        Acc e[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) e[k] = term(i + k * stride);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s[k] += e[k];
+    }
+    for (; i < m; i += stride) s[0] += term(i);
+    return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+}
+
+template <class Acc>
+__device__ __forceinline__ Acc squared_error(const float* C, const float* tgt, int64_t i) {
+    const Acc e = (Acc)C[i] - (Acc)tgt[i];
+    return e * e;
+}
+
+__global__ __launch_bounds__(kLossBlock) void k_l2_one(const float* __restrict__ C, const float* __restrict__ tgt,
+                                                      int64_t n, float scale2, float* __restrict__ dC,
+                                                      float* __restrict__ loss) {
+    __shared__ float part[kLossBlock / 64];
+    const int64_t m = n * 3;
+    const float s = strided_sum<float>(threadIdx.x, kLossBlock, m, [&](int64_t i) {
+        const float e = C[i] - tgt[i];
+        dC[i] = scale2 * e;
+        return e * e;
+    });
+    const float t = block_sum<float, kLossBlock>(s, part);
+    if (threadIdx.x == 0) *loss = t / 3.0f / (float)n;
+}
+
+__global__ __launch_bounds__(kBlock) void k_l2_parts(const float* __restrict__ C, const float* __restrict__ tgt,
+                                                     int64_t n, float* __restrict__ parts) {
+    __shared__ float part[kBlock / 64];
+    const float s = strided_sum<float>((int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)kLossParts * kBlock, n * 3,
+                                       [&](int64_t i) { return squared_error<float>(C, tgt, i); });
+    const float t = block_sum<float, kBlock>(s, part);
+    if (threadIdx.x == 0) parts[blockIdx.x] = t;
+}
+
+// loss non-NULL: block 0 first sums the kLossParts partial sums that dC starts
+// with; it alone writes those entries (its first kBlock).
 __global__ __launch_bounds__(kBlock) void k_l2_grad(const float* __restrict__ C, const float* __restrict__ tgt,
-                                                    int64_t n, float scale2, float* __restrict__ dC) {
+                                                    int64_t n, float scale2, float* __restrict__ dC,
+                                                    float* __restrict__ loss) {
+    static_assert(kLossParts == kBlock, "block 0 owns the partial sums' place");
+    if (loss && blockIdx.x == 0) {
+        __shared__ float part[kBlock / 64];
+        const float t = block_sum<float, kBlock>(dC[threadIdx.x], part);
+        if (threadIdx.x == 0) *loss = t / 3.0f / (float)n;
+    }
     const int64_t m = n * 3;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < m; i += (int64_t)gridDim.x * kBlock)
         dC[i] = scale2 * (C[i] - tgt[i]);
 }
 
-template <class Acc>
-__global__ __launch_bounds__(kLossBlock) void k_l2_loss(const float* __restrict__ C, const float* __restrict__ tgt,
-                                                       int64_t n, Acc* __restrict__ loss) {
-    __shared__ Acc part[kLossBlock / 64];
-    const int64_t m = n * 3;
-    Acc s = 0;
-    for (int64_t i = threadIdx.x; i < m; i += kLossBlock) {
-        const Acc e = (Acc)C[i] - (Acc)tgt[i];
-        s += e * e;
-    }
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        Acc t = 0;
-        for (int w = 0; w < kLossBlock / 64; ++w) t += part[w];
-        *loss = t / (Acc)3 / (Acc)n;
-    }
+__global__ __launch_bounds__(kLossBlock) void k_l2_loss_fp64(const float* __restrict__ C, const float* __restrict__ tgt,
+                                                            int64_t n, double* __restrict__ loss) {
+    __shared__ double part[kLossBlock / 64];
+    const double s = strided_sum<double>(threadIdx.x, kLossBlock, n * 3,
+                                         [&](int64_t i) { return squared_error<double>(C, tgt, i); });
+    const double t = block_sum<double, kLossBlock>(s, part);
+    if (threadIdx.x == 0) *loss = t / 3.0 / (double)n;
 }
 
 template <int NIN>
@@ -464,18 +530,20 @@ hipError_t launch_mlp(const float* W, int mlp_in, bool bf16, const RayParams& rp
 }
 
 hipError_t launch_l2(const float* C, const float* tgt, int64_t n, float* dC, float* loss, hipStream_t s) {
-    if (dC) {
-        int64_t blocks = (n * 3 + kBlock - 1) / kBlock;
-        if (blocks > 2048) blocks = 2048;
-        const float scale2 = (float)(2.0 / (3.0 * (double)n));  // 2 / (3 n), rounded once on the host
-        hipLaunchKernelGGL(k_l2_grad, dim3((unsigned)blocks), dim3(kBlock), 0, s, C, tgt, n, scale2, dC);
+    const float scale2 = (float)(2.0 / (3.0 * (double)n));  // 2 / (3 n), rounded once on the host
+    if (loss && n * 3 <= kLossOneBlock) {
+        hipLaunchKernelGGL(k_l2_one, dim3(1), dim3(kLossBlock), 0, s, C, tgt, n, scale2, dC, loss);
+        return hipGetLastError();
     }
-    if (loss) hipLaunchKernelGGL(k_l2_loss<float>, dim3(1), dim3(kLossBlock), 0, s, C, tgt, n, loss);
+    if (loss) hipLaunchKernelGGL(k_l2_parts, dim3(kLossParts), dim3(kBlock), 0, s, C, tgt, n, dC);
+    int64_t blocks = (n * 3 + kBlock - 1) / kBlock;
+    if (blocks > 2048) blocks = 2048;
+    hipLaunchKernelGGL(k_l2_grad, dim3((unsigned)blocks), dim3(kBlock), 0, s, C, tgt, n, scale2, dC, loss);
     return hipGetLastError();
 }
 
 hipError_t launch_l2_fp64(const float* C, const float* tgt, int64_t n, double* loss, hipStream_t s) {
-    hipLaunchKernelGGL(k_l2_loss<double>, dim3(1), dim3(kLossBlock), 0, s, C, tgt, n, loss);
+    hipLaunchKernelGGL(k_l2_loss_fp64, dim3(1), dim3(kLossBlock), 0, s, C, tgt, n, loss);
     return hipGetLastError();
 }
 
@@ -520,7 +588,7 @@ hipError_t launch_occ_pyramid(const float2* occ, int Mx, int My, float2* mips, i
 // ---------------------------------------------------------------------------
 // Interval-span regulariser (Eq. 5): weight * sum (z_max - z_min)^2 and its
 // gradient 2 weight (z_max - z_min) (-1, +1) added to grad_occ, in float32.
-// The loss is summed by one workgroup in a fixed order (see k_l2_loss).
+// The loss is summed by one workgroup in a fixed order.
 // ---------------------------------------------------------------------------
 __global__ void k_occ_grad(const float2* __restrict__ occ, int64_t cells, float weight, float2* __restrict__ grad) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cells; i += (int64_t)gridDim.x * blockDim.x) {
@@ -536,20 +604,13 @@ __global__ void k_occ_grad(const float2* __restrict__ occ, int64_t cells, float 
 __global__ __launch_bounds__(kLossBlock) void k_occ_loss(const float2* __restrict__ occ, int64_t cells, float weight,
                                                         float* __restrict__ loss) {
     __shared__ float part[kLossBlock / 64];
-    float s = 0.0f;
-    for (int64_t i = threadIdx.x; i < cells; i += kLossBlock) {
+    const float s = strided_sum<float>(threadIdx.x, kLossBlock, cells, [&](int64_t i) {
         const float2 z = occ[i];
         const float span = z.y - z.x;
-        s += span * span;
-    }
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float t = 0.0f;
-        for (int w = 0; w < kLossBlock / 64; ++w) t += part[w];
-        *loss = weight * t;
-    }
+        return span * span;
+    });
+    const float t = block_sum<float, kLossBlock>(s, part);
+    if (threadIdx.x == 0) *loss = weight * t;
 }
 
 hipError_t launch_occ_loss(const float* occ, int64_t cells, float weight, float* loss, float* grad, hipStream_t s) {
