@@ -186,7 +186,7 @@ __device__ __forceinline__ void scatter_batch_runs(const SceneDev& sc, float* gV
 
 // One replayed sample: optical depth, density, activated colours/features
 // and, for the soft occupancy, its value and derivatives.
-template <class S, bool kSoft>
+template <class S, bool kSoft, bool kNarrow>
 __device__ __forceinline__ void replay_sample(const SceneDev& sc, const RayParams& rp, float3 o, float3 d, int kq,
                                               bool act, float& a, float& tau, float* v, Corners& cn, OccValue& oc) {
     a = 0.0f;
@@ -197,10 +197,10 @@ __device__ __forceinline__ void replay_sample(const SceneDev& sc, const RayParam
     for (int c = 0; c < 7; ++c) v[c] = 0.0f;
     if (act) {
         const float3 p = lattice_point(kq, o, d, rp.delta);
-        cn = corners_of(sc, p);
+        cn = corners_of<false, kNarrow>(sc, p);
         if (kSoft) oc = occ_value(sc, p, rp.occ_inv_eps);
         float t[8];
-        gather_features_split<S, false>(sc, cn, t);
+        gather_features_split<S, kNarrow>(sc, cn, t);
         tau = __expf(t[0]);
         a = tau * rp.delta;
 #pragma unroll
@@ -293,10 +293,42 @@ __global__ __launch_bounds__(256) void k_order_scatter(const int32_t* __restrict
     }
 }
 
-template <class S, bool kSoft>
+// The whole order of a small batch in one block and one launch (the four
+// launches above take 4.5 us each however small the batch).
+constexpr int kOrderSmallThreads = 1024;
+constexpr int64_t kOrderSmall = 16384;
+
+__global__ __launch_bounds__(kOrderSmallThreads) void k_order_small(const int32_t* __restrict__ n_eval, int n,
+                                                                    int nbins, int* __restrict__ hdr,
+                                                                    int32_t* __restrict__ order) {
+    __shared__ int cnt[kOrderBins], next[kOrderBins];
+    const int t = threadIdx.x;
+    if (t < kOrderBins) cnt[t] = 0;
+    __syncthreads();
+    for (int r = t; r < n; r += kOrderSmallThreads) atomicAdd(&cnt[batch_bin(n_eval[r], nbins)], 1);
+    __syncthreads();
+    if (t < 64) {  // lane t: bin nbins - 1 - t; a 65th bin (0) follows them all
+        const int b = nbins - 1 - t, c = b >= 0 ? cnt[b] : 0;
+        int sum = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_up(sum, off);
+            if (t >= off) sum += v;
+        }
+        if (b >= 0) next[b] = sum - c;
+        if (t == 63 && b > 0) next[0] = sum;
+    }
+    if (t < kOrderBins) hdr[t] = t < nbins ? cnt[t] : 0;
+    if (t == kOrderBins) hdr[kOrderCounter] = 0;
+    __syncthreads();
+    for (int r = t; r < n; r += kOrderSmallThreads) order[atomicAdd(&next[batch_bin(n_eval[r], nbins)], 1)] = r;
+}
+
+template <class S, bool kSoft, bool kNarrow>
 __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams rp, const float* __restrict__ o_,
                                                        const float* __restrict__ d_, int64_t n,
-                                                       const int32_t* __restrict__ order, unsigned int* __restrict__ next_ray,
+                                                       const int32_t* __restrict__ order, const int* __restrict__ sched,
+                                                       unsigned int* __restrict__ next_ray,
                                                        const float* __restrict__ Ts,
                                                        const int32_t* __restrict__ n_eval,
                                                        const float* __restrict__ BW, const float* __restrict__ G8,
@@ -338,7 +370,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
                 }
 #pragma unroll
                 for (int k = 0; k < kBatchSlots; ++k)
-                    if (s == k) btot[k] = t;
+                    btot[k] = s == k ? t : btot[k];
             }
         } else {
             float carry = 0.0f;
@@ -349,7 +381,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
                 float a, tau, v[7];
                 Corners cn;
                 OccValue oc;
-                replay_sample<S, kSoft>(sc, rp, o, d, kq, act, a, tau, v, cn, oc);
+                replay_sample<S, kSoft, kNarrow>(scene_argument(), rp, o, d, kq, act, a, tau, v, cn, oc);
                 const float incl = g_scan_incl(a, gl);
                 const float excl = g_shift_up1(incl);
                 const float w = act ? __expf(-(carry + excl)) * (-expm1f(-a)) * (kSoft ? oc.m : 1.0f) : 0.0f;
@@ -359,7 +391,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
                 const float tot = g_sum(w * gv);
 #pragma unroll
                 for (int s = 0; s < kBatchSlots; ++s)
-                    if ((b >> 4) == s && gl == (b & 15)) btot[s] = tot;
+                    btot[s] = (b >> 4) == s && gl == (b & 15) ? tot : btot[s];
                 carry += __shfl(incl, kGroup - 1, kGroup);
                 done += nb_eff;
                 ++b;
@@ -387,7 +419,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
             float a, tau, v[7];
             Corners cn;
             OccValue oc;
-            replay_sample<S, kSoft>(sc, rp, o, d, kq, act, a, tau, v, cn, oc);
+            replay_sample<S, kSoft, kNarrow>(scene_argument(), rp, o, d, kq, act, a, tau, v, cn, oc);
             const float incl = g_scan_incl(a, gl);
             const float excl = g_shift_up1(incl);
             const float Ti = __expf(-(carry + excl));
@@ -410,7 +442,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
             gt[0] = (Tnext * msoft * gv - suffix - Tn * gT) * rp.delta * tau;
 #pragma unroll
             for (int c = 0; c < 7; ++c) gt[c + 1] = w * g7[c] * v[c] * (1.0f - v[c]);
-            scatter_batch_runs(sc, gV, gxy, gxz, gyz, stage, act, cn, gt, gl, lane);
+            scatter_batch_runs(scene_argument(), gV, gxy, gxz, gyz, stage, act, cn, gt, gl, lane);
             if (kSoft && gocc) scatter_occ(gocc, act, oc, w0 * gv, gl, lane);  // dL/dM = w0 (g7 . v)
             carry += __shfl(incl, kGroup - 1, kGroup);
             done += nb_eff;
@@ -419,15 +451,18 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
         });
     };
     // Four rays per wave and turn, the next turn's requested ahead.  The
-    // counter is unsigned: it ends below n + 8 x 4 per wave < 2^32.
+    // counter is unsigned: it ends below n + 8 x 4 per wave < 2^32.  Rays
+    // without samples, last in the order, are not handed out: the counter
+    // serves a request every 8 ns, 0.6 ms for 300,000 of them.
+    const int64_t live = n - sched[0];
     unsigned int first = 0u;
     if (lane == 0) first = atomicAdd(next_ray, 4u);
     int64_t base = (int64_t)(unsigned int)__shfl((int)first, 0);
-    while (base < n) {
+    while (base < live) {
         unsigned int ahead = 0u;
         if (lane == 0) ahead = atomicAdd(next_ray, 4u);
         const int64_t idx = base + (gid & 3);
-        if (idx < n) ray_body(order[idx]);
+        if (idx < live) ray_body(order[idx]);
         base = (int64_t)(unsigned int)__shfl((int)ahead, 0);
     }
 }
@@ -443,29 +478,28 @@ hipError_t launch_march_bwd(const SceneDev& sc, bool bf16, const RayParams& rp, 
     const int nbins = (rp.n_max + kGroup - 1) / kGroup + 1;
     const int64_t sort_blocks = min((n + 4095) / 4096, (int64_t)1024);
     const int64_t sort_chunk = (n + sort_blocks - 1) / sort_blocks;
-    hipLaunchKernelGGL(k_order_clear, dim3(1), dim3(64), 0, s, sched);
-    hipLaunchKernelGGL(k_order_hist, dim3((unsigned)sort_blocks), dim3(256), 0, s, n_eval, n, sort_chunk, nbins, sched);
-    hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(64), 0, s, nbins, sched);
-    hipLaunchKernelGGL(k_order_scatter, dim3((unsigned)sort_blocks), dim3(256), 0, s, n_eval, n, sort_chunk, nbins,
-                       sched, order);
+    if (n <= kOrderSmall) {
+        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(kOrderSmallThreads), 0, s, n_eval, (int)n, nbins, sched, order);
+    } else {
+        hipLaunchKernelGGL(k_order_clear, dim3(1), dim3(64), 0, s, sched);
+        hipLaunchKernelGGL(k_order_hist, dim3((unsigned)sort_blocks), dim3(256), 0, s, n_eval, n, sort_chunk, nbins,
+                           sched);
+        hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(64), 0, s, nbins, sched);
+        hipLaunchKernelGGL(k_order_scatter, dim3((unsigned)sort_blocks), dim3(256), 0, s, n_eval, n, sort_chunk, nbins,
+                           sched, order);
+    }
     unsigned int* next_ray = reinterpret_cast<unsigned int*>(sched + kOrderCounter);
     const dim3 grid((unsigned)min((n + kGroupsPerBlock - 1) / kGroupsPerBlock, (int64_t)2048)), block(kBlock);
-    const bool soft = rp.occ_inv_eps > 0.0f;
-    if (bf16) {
-        if (soft)
-            hipLaunchKernelGGL((k_march_bwd<BF16Store, true>), grid, block, 0, s, sc, rp, o, d, n, order, next_ray, T,
-                               n_eval, batch_wv, G8, gV, gxy, gxz, gyz, gocc);
-        else
-            hipLaunchKernelGGL((k_march_bwd<BF16Store, false>), grid, block, 0, s, sc, rp, o, d, n, order, next_ray, T,
-                               n_eval, batch_wv, G8, gV, gxy, gxz, gyz, gocc);
-    } else {
-        if (soft)
-            hipLaunchKernelGGL((k_march_bwd<F32Store, true>), grid, block, 0, s, sc, rp, o, d, n, order, next_ray, T,
-                               n_eval, batch_wv, G8, gV, gxy, gxz, gyz, gocc);
-        else
-            hipLaunchKernelGGL((k_march_bwd<F32Store, false>), grid, block, 0, s, sc, rp, o, d, n, order, next_ray, T,
-                               n_eval, batch_wv, G8, gV, gxy, gxz, gyz, gocc);
-    }
+    typedef void (*Form)(SceneDev, RayParams, const float*, const float*, int64_t, const int32_t*, const int*,
+                         unsigned int*, const float*, const int32_t*, const float*, const float*, float*, float*,
+                         float*, float*, float*);
+    static constexpr Form forms[2][2][2] = {
+        {{k_march_bwd<F32Store, false, false>, k_march_bwd<F32Store, false, true>},
+         {k_march_bwd<F32Store, true, false>, k_march_bwd<F32Store, true, true>}},
+        {{k_march_bwd<BF16Store, false, false>, k_march_bwd<BF16Store, false, true>},
+         {k_march_bwd<BF16Store, true, false>, k_march_bwd<BF16Store, true, true>}}};
+    hipLaunchKernelGGL(forms[bf16][rp.occ_inv_eps > 0.0f][narrow_scene(sc, bf16 ? OM_BF16 : OM_F32)], grid, block, 0, s,
+                       sc, rp, o, d, n, order, sched, next_ray, T, n_eval, batch_wv, G8, gV, gxy, gxz, gyz, gocc);
     return hipGetLastError();
 }
 

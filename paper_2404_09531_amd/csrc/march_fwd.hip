@@ -415,7 +415,7 @@ hipError_t launch_mark(const SceneDev& sc, const RayParams& rp, const float* o, 
 // Whether every feature source can be addressed with 32-bit byte offsets and
 // 24-bit index factors (RowAddr<true>): the full-size scenes of the benchmark
 // can, in every storage type (their float32 grid is 4 GiB exactly).
-static bool narrow_scene(const SceneDev& sc, int dtype) {
+bool narrow_scene(const SceneDev& sc, int dtype) {
     const uint64_t bytes = dtype == OM_F32 ? 32 : dtype == OM_BF16 ? 16 : 8, most = 1ull << 32, f24 = 1ull << 24;
     const uint64_t grid = sc.blk_shift > 0 ? ((uint64_t)sc.n_blocks + 1) * sc.blk_verts
                                            : (uint64_t)sc.Lx * (uint64_t)sc.Ly * (uint64_t)sc.Lz;

@@ -8,6 +8,9 @@
 
 namespace omerf {
 
+// Whether the marches address a scene's rows with 32-bit byte offsets.
+bool narrow_scene(const SceneDev& sc, int dtype);
+
 hipError_t launch_place(const SceneDev& sc, const RayParams& rp, const float* o, const float* d, int64_t n,
                         int32_t* k_out, int32_t* n_placed, hipStream_t s);
 hipError_t launch_mark(const SceneDev& sc, const RayParams& rp, const float* o, const float* d, int64_t n,
@@ -34,6 +37,8 @@ hipError_t launch_occ_loss(const float* occ, int64_t cells, float weight, float*
 hipError_t launch_range(const float* x, int64_t n, float* minmax, uint32_t* keys, hipStream_t s);
 hipError_t launch_quantize(const float* x, int64_t n, const float* lo, const float* inv, uint8_t* out, hipStream_t s);
 hipError_t launch_blocks_mark(const SceneDev& sc, int shift, int bnx, int bny, int bnz, int32_t* mark, hipStream_t s);
+hipError_t launch_blocks_number(int32_t* mark, int64_t n, hipStream_t s);
+hipError_t launch_blocks_first(int32_t* mark, int id, hipStream_t s);
 hipError_t launch_blocks_fill(const SceneDev& sc, int shift, int bnx, int bny, int bnz, const int32_t* idx,
                               int64_t n_blocks, int units, void* atlas, hipStream_t s);
 hipError_t launch_cast_bf16(const float* src, int64_t n, uint16_t* dst, hipStream_t s);
