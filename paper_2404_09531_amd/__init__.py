@@ -628,9 +628,11 @@ def quantize_features(tensors: Dict[str, torch.Tensor]):
     """Bake float32 grid and planes to 8-bit storage (Sec. 4.4): per source,
     its channel ranges, (lo, step) and codes.  Returns ({source: uint8
     tensor}, (lo, step) as float32 [4, 8] lists for Scene(..., quant=...))."""
+    keys = ("grid", "plane_xy", "plane_xz", "plane_yz")
+    ranges = torch.stack([feature_range(tensors[key]) for key in keys]).cpu()  # one wait for the four
     codes, los, steps = {}, [], []
-    for key in ("grid", "plane_xy", "plane_xz", "plane_yz"):
-        lo, step = quant_params(feature_range(tensors[key]).cpu())
+    for key, minmax in zip(keys, ranges):
+        lo, step = quant_params(minmax)
         codes[key] = quantize_u8(tensors[key], lo, step)
         los.append(lo)
         steps.append(step)

@@ -7,7 +7,6 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <vector>
 
 #include "../../include/omerf.h"
 #include "omerf_device.h"
@@ -651,21 +650,19 @@ int64_t om_sparse_grid_index(const om_scene* scene, int block_shift, int32_t* gr
     }
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = launch_blocks_mark(scene->dev, block_shift, bn[0], bn[1], bn[2], grid_blocks, s);
-    std::vector<int32_t> mark((size_t)n);
-    if (e == hipSuccess) e = hipMemcpyAsync(mark.data(), grid_blocks, (size_t)n * 4, hipMemcpyDeviceToHost, s);
+    // Numbered on the device; only the count comes back, in entry 0 (negated
+    // if that block is kept), which then gets its own id.
+    if (e == hipSuccess) e = launch_blocks_number(grid_blocks, n, s);
+    int32_t count = 0;
+    if (e == hipSuccess) e = hipMemcpyAsync(&count, grid_blocks, sizeof count, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = launch_blocks_first(grid_blocks, count < 0 ? 1 : 0, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         hip_status(e, "om_sparse_grid_index");
         return -1;
     }
-    int64_t kept = 0;
-    for (int64_t i = 0; i < n; ++i) mark[(size_t)i] = mark[(size_t)i] ? (int32_t)(++kept) : 0;
-    e = hipMemcpyAsync(grid_blocks, mark.data(), (size_t)n * 4, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-        hip_status(e, "om_sparse_grid_index");
-        return -1;
-    }
+    const int64_t kept = count < 0 ? -(int64_t)count : count;
     ok();
     return kept;
 }
