@@ -227,9 +227,9 @@ __device__ __forceinline__ void scatter_occ(float* gocc, bool act, const OccValu
 // A wave's four groups walk their rays in step, so a wave waits for its
 // longest ray, and the kernel waits for its slowest wave.  The rays are
 // therefore counting-sorted by their number of 16-sample batches,
-// descending (k_order_*), and each wave takes the next four rays of that
-// order from a counter whenever it is free: a wave's rays have the same
-// batch count, and the short rays at the end even out the finish.
+// descending (k_order_*), and each wave takes four rays of that order at a
+// time (hand_out): a wave's rays have the same batch count, and the short
+// rays at the end even out the finish.
 //
 // Scheduling words in the workspace (int32): bins [0, 65), cursors
 // [65, 130), the hand-out counter at kOrderCounter.
@@ -322,6 +322,34 @@ __global__ __launch_bounds__(kOrderSmallThreads) void k_order_small(const int32_
     if (t == kOrderBins) hdr[kOrderCounter] = 0;
     __syncthreads();
     for (int r = t; r < n; r += kOrderSmallThreads) order[atomicAdd(&next[batch_bin(n_eval[r], nbins)], 1)] = r;
+}
+
+// Rays [from, to) of the order, four per wave and turn.  A wave's first
+// `turns` turns go by its number, further ones by tickets from the counter,
+// `turns` each and requested ahead.  One counter serves a ticket every 40 ns,
+// whatever the waves do in between (a fused step of 4,096 rays took 299 us with
+// two tickets per wave and turn, 211 with none; 16,384 rays 931 and 725), so there are some eight tickets per wave in all,
+// and no more waves than the chip holds: a block that had to wait would start
+// its long first rays last.  The counter is unsigned and ends below 2^32.
+template <class Body>
+__device__ __forceinline__ void hand_out(unsigned int* next_ray, int64_t from, int64_t to, int gid, int lane,
+                                         Body&& body) {
+    const int64_t waves = (int64_t)gridDim.x * (kGroupsPerBlock / 4);
+    const int64_t wave = (int64_t)blockIdx.x * (kGroupsPerBlock / 4) + (gid >> 2);
+    const int64_t turns = max((int64_t)1, min((int64_t)16, (to - from) / (4 * 8 * waves)));
+    const int64_t handed = from + 4 * turns * waves;  // by number
+    // By number, turn k of all waves together: equal shares of a sorted order.
+    int64_t base = from + 4 * wave, stride = 4 * waves;
+    while (base < to) {
+        unsigned int ahead = 0u;
+        if (handed < to && lane == 0) ahead = atomicAdd(next_ray, (unsigned int)(4 * turns));
+        for (int64_t k = 0; k < turns; ++k) {
+            const int64_t idx = base + k * stride + (gid & 3);
+            if (idx < to) body(idx);
+        }
+        base = handed + (int64_t)(unsigned int)__shfl((int)ahead, 0);
+        stride = 4;
+    }
 }
 
 template <class S, bool kSoft, bool kNarrow>
@@ -450,21 +478,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
             return done >= ne;
         });
     };
-    // Four rays per wave and turn, the next turn's requested ahead.  The
-    // counter is unsigned: it ends below n + 8 x 4 per wave < 2^32.  Rays
-    // without samples, last in the order, are not handed out: the counter
-    // serves a request every 8 ns, 0.6 ms for 300,000 of them.
-    const int64_t live = n - sched[0];
-    unsigned int first = 0u;
-    if (lane == 0) first = atomicAdd(next_ray, 4u);
-    int64_t base = (int64_t)(unsigned int)__shfl((int)first, 0);
-    while (base < live) {
-        unsigned int ahead = 0u;
-        if (lane == 0) ahead = atomicAdd(next_ray, 4u);
-        const int64_t idx = base + (gid & 3);
-        if (idx < live) ray_body(order[idx]);
-        base = (int64_t)(unsigned int)__shfl((int)ahead, 0);
-    }
+    // Rays without samples, last in the order, are not handed out.
+    hand_out(next_ray, 0, n - sched[0], gid, lane, [&](int64_t idx) { ray_body(order[idx]); });
 }
 
 hipError_t launch_march_bwd(const SceneDev& sc, bool bf16, const RayParams& rp, const float* o, const float* d,
@@ -472,9 +487,7 @@ hipError_t launch_march_bwd(const SceneDev& sc, bool bf16, const RayParams& rp, 
                             int32_t* order, int* sched, float* gV, float* gxy, float* gxz, float* gyz, float* gocc,
                             hipStream_t s) {
     // Longest-first order (counting sort by batch count), then persistent
-    // blocks whose waves take rays from it on demand.  2048 blocks of 4 waves
-    // cover every wave slot of the device (4 per SIMD); blocks beyond the
-    // slots start when the order is handed out and leave at once.
+    // blocks, as many as the chip holds (4 waves per SIMD).
     const int nbins = (rp.n_max + kGroup - 1) / kGroup + 1;
     const int64_t sort_blocks = min((n + 4095) / 4096, (int64_t)1024);
     const int64_t sort_chunk = (n + sort_blocks - 1) / sort_blocks;
@@ -489,7 +502,7 @@ hipError_t launch_march_bwd(const SceneDev& sc, bool bf16, const RayParams& rp, 
                            sched, order);
     }
     unsigned int* next_ray = reinterpret_cast<unsigned int*>(sched + kOrderCounter);
-    const dim3 grid((unsigned)min((n + kGroupsPerBlock - 1) / kGroupsPerBlock, (int64_t)2048)), block(kBlock);
+    const dim3 grid((unsigned)min((n + kGroupsPerBlock - 1) / kGroupsPerBlock, (int64_t)(256 * 4))), block(kBlock);
     typedef void (*Form)(SceneDev, RayParams, const float*, const float*, int64_t, const int32_t*, const int*,
                          unsigned int*, const float*, const int32_t*, const float*, const float*, float*, float*,
                          float*, float*, float*);
