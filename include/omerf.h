@@ -393,6 +393,18 @@ int om_render_fwd_bwd_l2(const om_scene* scene, const float* o, const float* d, 
 int64_t om_render_fwd_bwd_l2_workspace_size(int64_t n, const om_params* p);
 
 /*
+ * Workspace beyond om_render_fwd_bwd_l2_workspace_size(n, p) with which
+ * om_render_fwd_bwd_l2 keeps a record per 16-sample batch between the forward
+ * and the backward, instead of replaying the samples, and sums the XZ and YZ
+ * gradients by tiles instead of one float atomic per segment: bytes to add (p:
+ * only n_max is read), 0 where that would not pay for this scene and batch, -1
+ * (with om_last_error set) on invalid arguments.  A call whose workspace holds
+ * them uses them; with a smaller one it computes the same without.  At most
+ * about 5 GB; batches with more samples keep the records of their longest rays.
+ */
+int64_t om_render_fwd_bwd_l2_records_size(const om_scene* scene, int64_t n, const om_params* p);
+
+/*
  * om_render_fwd_bwd_l2 for callers that cannot allocate device memory: code
  * under HIP graph capture, tight serving or training loops, harnesses that
  * forbid hipMalloc.  Same arguments and results as om_render_fwd_bwd_l2

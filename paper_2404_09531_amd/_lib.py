@@ -22,7 +22,7 @@ EXPORTS = ("om_scene_create", "om_scene_update", "om_scene_destroy", "om_occupan
            "om_build_occupancy_mips", "om_place_samples", "om_march",
            "om_deferred_mlp", "om_render",
            "om_render_backward", "om_render_backward_ex", "om_render_backward_workspace_size", "om_smooth_loss", "om_render_fwd_bwd_l2", "om_render_fwd_bwd_l2_workspace_size",
-           "om_render_fwd_bwd_l2_noalloc", "om_render_fwd_bwd_l2_noalloc_max_bytes",
+           "om_render_fwd_bwd_l2_records_size", "om_render_fwd_bwd_l2_noalloc", "om_render_fwd_bwd_l2_noalloc_max_bytes",
            "om_occ_interval_loss", "om_feature_range", "om_quant_params", "om_quantize_u8",
            "om_sparse_grid_index", "om_sparse_grid_fill",
            "om_cast_bf16", "om_order_rays", "om_order_rays_workspace_size", "om_gather_rows", "om_scatter_rows",
@@ -107,6 +107,7 @@ def lib() -> ctypes.CDLL:
                                            POINTER(OmFwdOut), c_void_p, c_int64, c_void_p, POINTER(OmGrads),
                                            c_void_p]
         L.om_render_fwd_bwd_l2_workspace_size.argtypes = [c_int64, POINTER(OmParams)]
+        L.om_render_fwd_bwd_l2_records_size.argtypes = [c_void_p, c_int64, POINTER(OmParams)]
         L.om_render_fwd_bwd_l2_noalloc.argtypes = [c_void_p, c_void_p, c_void_p, c_int64, POINTER(OmParams),
                                                    c_void_p, POINTER(OmFwdOut), c_void_p, POINTER(OmGrads), c_void_p]
         L.om_render_fwd_bwd_l2_noalloc_max_bytes.argtypes = []
@@ -121,6 +122,7 @@ def lib() -> ctypes.CDLL:
                             "om_render_fwd_bwd_l2_noalloc_max_bytes", "om_occupancy_mips_size"):
                 getattr(L, name).restype = c_int
         L.om_render_fwd_bwd_l2_workspace_size.restype = c_int64
+        L.om_render_fwd_bwd_l2_records_size.restype = c_int64
         L.om_render_fwd_bwd_l2_noalloc_max_bytes.restype = c_int64
         L.om_occupancy_mips_size.restype = c_int64
         L.om_sparse_grid_index.restype = c_int64

@@ -341,7 +341,7 @@ int om_march(const om_scene* scene, const float* o, const float* d, int64_t n, c
     int rc = check_fwd(scene, o, d, n, p, out, true, false, &rp);
     if (rc != OM_OK || n == 0) return rc == OM_OK ? ok() : rc;
     return hip_status(launch_march_fwd(scene->dev, scene->desc.dtype, rp, o, d, n, out->F, out->T, out->n_placed, out->n_eval,
-                                       out->batch_wv, (hipStream_t)stream), "om_march");
+                                       out->batch_wv, nullptr, (hipStream_t)stream), "om_march");
 }
 
 int om_deferred_mlp(const om_scene* scene, const float* d, int64_t n, const om_params* p, const om_fwd_out* out,
@@ -360,7 +360,7 @@ int om_render(const om_scene* scene, const float* o, const float* d, int64_t n, 
     if (rc != OM_OK || n == 0) return rc == OM_OK ? ok() : rc;
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = launch_march_fwd(scene->dev, scene->desc.dtype, rp, o, d, n, out->F, out->T, out->n_placed,
-                                    out->n_eval, out->batch_wv, s);
+                                    out->n_eval, out->batch_wv, nullptr, s);
     if (e != hipSuccess) return hip_status(e, "om_render (march)");
     e = launch_mlp(scene->dev.mlp, scene->dev.mlp_in, mlp_in_bf16(scene, p), rp, d, n, out->F, out->T, out->n_eval, out->C, s);
     return hip_status(e, "om_render (mlp)");
@@ -398,21 +398,41 @@ int check_backward(const om_scene* scene, const float* o, const float* d, int64_
     return OM_OK;
 }
 
+// The backward workspace (om_render_backward_workspace_size(n) bytes, 256-byte
+// aligned): the per-ray hand-over, the ray order, its scheduling words.
+struct BwdWorkspace {
+    float* G8;
+    int32_t* order;
+    int* sched;
+    BwdWorkspace(void* ws, int64_t n) {
+        char* p = static_cast<char*>(ws);
+        G8 = reinterpret_cast<float*>(p);
+        p += (n * 8 * (int64_t)sizeof(float) + 255) / 256 * 256;
+        order = reinterpret_cast<int32_t*>(p);
+        sched = reinterpret_cast<int*>(p + (n * (int64_t)sizeof(int32_t) + 255) / 256 * 256);
+    }
+};
+
 // MLP backward into G8 (per-ray dL/dF and background term), then the march
-// backward that reads it.  `ws` is the backward workspace
-// (om_render_backward_workspace_size(n) bytes, 256-byte aligned).
+// backward that reads it, over rays ordered here by their samples.
 hipError_t backward_launch(const om_scene* scene, const RayParams& rp, const float* o, const float* d, int64_t n,
                            const float* F, const float* T, const int32_t* n_eval, const float* batch_wv,
                            const float* dC, const float* dF, void* ws, const om_grads* g, hipStream_t s) {
-    char* p = static_cast<char*>(ws);
-    float* G8 = reinterpret_cast<float*>(p);
-    int32_t* order = reinterpret_cast<int32_t*>(p + (n * 8 * (int64_t)sizeof(float) + 255) / 256 * 256);
-    int* sched = reinterpret_cast<int*>(reinterpret_cast<char*>(order) +
-                                        (n * (int64_t)sizeof(int32_t) + 255) / 256 * 256);
-    hipError_t e = launch_mlp_bwd(scene->dev.mlp, scene->dev.mlp_in, rp, F, d, n_eval, dC, dF, n, G8, g->mlp, s);
+    const BwdWorkspace w(ws, n);
+    hipError_t e = launch_mlp_bwd(scene->dev.mlp, scene->dev.mlp_in, rp, F, d, n_eval, dC, dF, n, w.G8, g->mlp, s);
+    if (e == hipSuccess) e = launch_bwd_order(n_eval, n, rp.n_max, w.order, w.sched, nullptr, s);
     if (e != hipSuccess) return e;
-    return launch_march_bwd(scene->dev, scene->desc.dtype == OM_BF16, rp, o, d, n, T, n_eval, batch_wv, G8, order,
-                            sched, g->grid, g->plane_xy, g->plane_xz, g->plane_yz, g->occ, s);
+    return launch_march_bwd(scene->dev, scene->desc.dtype == OM_BF16, rp, o, d, n, T, n_eval, batch_wv, w.G8, w.order,
+                            w.sched, nullptr, g->grid, g->plane_xy, g->plane_xz, g->plane_yz, g->occ, s);
+}
+
+// The part of a caller workspace of `bytes`, `need` of them in use, that
+// holds the fused step's batch records: NULL where they do not pay or do not
+// fit whole.
+void* records_part(const om_scene* scene, int64_t n, const RayParams& rp, void* workspace, int64_t bytes, int64_t need) {
+    const int64_t at = (need + 255) / 256 * 256;
+    const int64_t more = record_workspace(scene->dev, n, rp.n_max, nullptr, nullptr, nullptr);
+    return more > 0 && bytes - at >= more ? static_cast<char*>(workspace) + at : nullptr;
 }
 
 }  // namespace
@@ -438,6 +458,18 @@ int om_render_backward_ex(const om_scene* scene, const float* o, const float* d,
     const hipError_t e = backward_launch(scene, rp, o, d, n, saved->F, saved->T, saved->n_eval, saved->batch_wv, dL_dC,
                                          dL_dF, workspace, g, (hipStream_t)stream);
     return hip_status(e, "om_render_backward");
+}
+
+int64_t om_render_fwd_bwd_l2_records_size(const om_scene* scene, int64_t n, const om_params* p) {
+    RayParams rp;
+    if (!scene || n < 0 || n > ((int64_t)1 << 31) - 1) {
+        fail(OM_ERR_INVALID, "scene must be non-NULL and n in [0, 2^31 - 1]");
+        return -1;
+    }
+    if (validate_params(p, &rp) != OM_OK) return -1;
+    if (n == 0 || scene->desc.dtype == OM_U8 || scene->desc.block_shift > 0) return 0;
+    const int64_t more = record_workspace(scene->dev, n, rp.n_max, nullptr, nullptr, nullptr);
+    return more > 0 ? more + 256 : 0;
 }
 
 int64_t om_render_fwd_bwd_l2_workspace_size(int64_t n, const om_params* p) {
@@ -480,22 +512,44 @@ int check_fwd_bwd_l2(const om_scene* scene, const float* o, const float* d, int6
 // the backward's workspace (om_render_backward_workspace_size: per-ray dL/dF
 // and background term, ray order, scheduling words) | per-batch sums of
 // w v]: forward with per-batch sums, loss gradient, MLP backward, march
-// backward.
+// backward.  With `records` the rays are counted and ordered first, so that
+// the forward can leave its batch records and the backward need not replay.
 int fwd_bwd_l2_launch(const om_scene* scene, const float* o, const float* d, int64_t n, const om_params* p,
-                      const RayParams& rp, const float* target, const om_fwd_out* out, void* workspace, float* loss,
-                      const om_grads* g, hipStream_t s, const char* who) {
+                      const RayParams& rp, const float* target, const om_fwd_out* out, void* workspace, void* records,
+                      float* loss, const om_grads* g, hipStream_t s, const char* who) {
     char* base = static_cast<char*>(workspace);
     float* dC = reinterpret_cast<float*>(base);
     char* bws = base + (n * 3 * (int64_t)sizeof(float) + 255) / 256 * 256;
     float* bw = reinterpret_cast<float*>(bws + om_render_backward_workspace_size(n));
-    hipError_t e = launch_march_fwd(scene->dev, scene->desc.dtype, rp, o, d, n, out->F, out->T, out->n_placed,
-                                    out->n_eval, bw, s);
+    const BwdWorkspace w(bws, n);
+    BatchRecords br{};
+    TileLists tl{};
+    const BatchRecords* brp = nullptr;
+    hipError_t e = hipSuccess;
+    if (records) {
+        record_workspace(scene->dev, n, rp.n_max, records, &br, &tl);
+        brp = &br;
+        e = launch_count(scene->dev, rp, o, d, n, out->n_placed, s);
+        if (e == hipSuccess) e = launch_bwd_order(out->n_placed, n, rp.n_max, w.order, w.sched, brp, s);
+        if (e != hipSuccess) return hip_status(e, who);
+    }
+    e = launch_march_fwd(scene->dev, scene->desc.dtype, rp, o, d, n, out->F, out->T, out->n_placed, out->n_eval, bw,
+                         brp, s);
     if (e != hipSuccess) return hip_status(e, who);
     e = launch_mlp(scene->dev.mlp, scene->dev.mlp_in, mlp_in_bf16(scene, p), rp, d, n, out->F, out->T, out->n_eval, out->C, s);
     if (e != hipSuccess) return hip_status(e, who);
     e = launch_l2(out->C, target, n, dC, loss, s);
     if (e != hipSuccess) return hip_status(e, who);
-    e = backward_launch(scene, rp, o, d, n, out->F, out->T, out->n_eval, bw, dC, nullptr, bws, g, s);
+    if (!records) {
+        e = backward_launch(scene, rp, o, d, n, out->F, out->T, out->n_eval, bw, dC, nullptr, bws, g, s);
+        return hip_status(e, who);
+    }
+    e = launch_mlp_bwd(scene->dev.mlp, scene->dev.mlp_in, rp, out->F, d, out->n_eval, dC, nullptr, n, w.G8, g->mlp, s);
+    if (e != hipSuccess) return hip_status(e, who);
+    e = launch_march_bwd(scene->dev, scene->desc.dtype == OM_BF16, rp, o, d, n, out->T, out->n_eval, bw, w.G8, w.order,
+                         w.sched, brp, g->grid, g->plane_xy, g->plane_xz, g->plane_yz, g->occ, s);
+    if (e != hipSuccess) return hip_status(e, who);
+    e = launch_tile_sums(scene->dev, br, tl, w.sched + kOrderRecords, g->plane_xz, g->plane_yz, s);
     return hip_status(e, who);
 }
 
@@ -534,7 +588,8 @@ int om_render_fwd_bwd_l2(const om_scene* scene, const float* o, const float* d, 
     if (workspace_bytes < need)
         return fail(OM_ERR_INVALID, "workspace holds %lld bytes, %lld needed", (long long)workspace_bytes,
                     (long long)need);
-    return fwd_bwd_l2_launch(scene, o, d, n, p, rp, target, out, workspace, loss, g, (hipStream_t)stream,
+    return fwd_bwd_l2_launch(scene, o, d, n, p, rp, target, out, workspace,
+                             records_part(scene, n, rp, workspace, workspace_bytes, need), loss, g, (hipStream_t)stream,
                              "om_render_fwd_bwd_l2");
 }
 
@@ -556,7 +611,7 @@ int om_render_fwd_bwd_l2_noalloc(const om_scene* scene, const float* o, const fl
     void* ws = nullptr;
     rc = scratch_for_current_device(&ws);
     if (rc != OM_OK) return rc;
-    return fwd_bwd_l2_launch(scene, o, d, n, p, rp, target, out, ws, loss, g, (hipStream_t)stream,
+    return fwd_bwd_l2_launch(scene, o, d, n, p, rp, target, out, ws, nullptr, loss, g, (hipStream_t)stream,
                              "om_render_fwd_bwd_l2_noalloc");
 }
 

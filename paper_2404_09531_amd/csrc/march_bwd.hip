@@ -163,6 +163,8 @@ __device__ __forceinline__ int class_row(int i, int q, float f, float& w) {
     return i + d;
 }
 
+// The batch's gradients on the grid and XY (kSides: and on XZ and YZ).
+template <bool kSides>
 __device__ __forceinline__ void scatter_batch_runs(const SceneDev& sc, float* gV, float* gxy, float* gxz, float* gyz,
                                                    Stage& st, bool act, const Corners& cn, const float* gt, int gl,
                                                    int lane) {
@@ -178,9 +180,11 @@ __device__ __forceinline__ void scatter_batch_runs(const SceneDev& sc, float* gV
         float w;
         int r = class_row(cn.jy, q, cn.uy, w);
         scatter_row_class(gxy, st, act, (uint32_t)r * (uint32_t)sc.Nx, cn.jx, w, cn.ux, gt, gl, lane);
-        r = class_row(cn.jz, q, cn.uz, w);
-        scatter_row_class(gxz, st, act, (uint32_t)r * (uint32_t)sc.Nx, cn.jx, w, cn.ux, gt, gl, lane);
-        scatter_row_class(gyz, st, act, (uint32_t)r * (uint32_t)sc.Ny, cn.jy, w, cn.uy, gt, gl, lane);
+        if (kSides) {
+            r = class_row(cn.jz, q, cn.uz, w);
+            scatter_row_class(gxz, st, act, (uint32_t)r * (uint32_t)sc.Nx, cn.jx, w, cn.ux, gt, gl, lane);
+            scatter_row_class(gyz, st, act, (uint32_t)r * (uint32_t)sc.Ny, cn.jy, w, cn.uy, gt, gl, lane);
+        }
     }
 }
 
@@ -232,12 +236,18 @@ __device__ __forceinline__ void scatter_occ(float* gocc, bool act, const OccValu
 // rays at the end even out the finish.
 //
 // Scheduling words in the workspace (int32): bins [0, 65), cursors
-// [65, 130), the hand-out counter at kOrderCounter.
+// [65, 130), the hand-out counters at kOrderCounter (of the rays that replay
+// and of those with records), from kOrderSlots per batch count what its rays'
+// place in the order, times the count, is from their first record, at
+// kOrderRecords the records in use and at kOrderRecorded the rays that have
+// records: the first of the order.
 // ---------------------------------------------------------------------------
 constexpr int kOrderBins = OM_MAX_SAMPLES / kGroup + 1;  // batch counts 0 .. n_max / 16
 constexpr int kOrderCursor = kOrderBins;
 constexpr int kOrderCounter = 2 * kOrderBins;
-static_assert(kOrderCounter < kBwdSchedWords, "scheduling words");
+constexpr int kOrderSlots = kOrderCounter + 2;
+constexpr int kOrderRecorded = kOrderRecords + 1;
+static_assert(kOrderSlots + kOrderBins <= kOrderRecords && kOrderRecorded < kBwdSchedWords, "scheduling words");
 
 __device__ __forceinline__ int batch_bin(int ne, int nbins) {
     return ne <= 0 ? 0 : min((ne + kGroup - 1) / kGroup, nbins - 1);
@@ -260,22 +270,42 @@ __global__ __launch_bounds__(256) void k_order_hist(const int32_t* __restrict__ 
         if (cnt[i]) atomicAdd(&hdr[i], cnt[i]);
 }
 
-// Start of each batch count's range in the order, longest first.
-__global__ __launch_bounds__(64) void k_order_scan(int nbins, int* __restrict__ hdr) {
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int b = nbins - 1; b >= 0; --b) {
-            hdr[kOrderCursor + b] = acc;
-            acc += hdr[b];
+// Start of each batch count's range in the order, longest first, and the
+// records of its rays: every ray takes as many as it has batches, whole rays
+// only, while the `cap` records last.  None below kRecordMin batches.
+__global__ __launch_bounds__(64) void k_order_scan(int nbins, int cap, int* __restrict__ hdr) {
+    if (threadIdx.x != 0) return;
+    int64_t batches = 0;
+    for (int b = 1; b < nbins; ++b) batches += (int64_t)hdr[b] * b;
+    if (batches < kRecordMin) cap = 0;
+    int acc = 0, slot = 0, recorded = 0;
+    for (int b = nbins - 1; b >= 0; --b) {
+        const int c = hdr[b];
+        hdr[kOrderCursor + b] = acc;
+        hdr[kOrderSlots + b] = (int)((unsigned)slot - (unsigned)acc * (unsigned)b);  // wraps, as its use does
+        if (b > 0 && acc == recorded) {
+            const int fit = min(c, (cap - slot) / b);
+            slot += fit * b;
+            recorded += fit;
         }
+        acc += c;
     }
+    hdr[kOrderRecords] = slot;
+    hdr[kOrderRecorded] = recorded;
+}
+
+// First record of the ray at `place` of the order with b batches, or -1.
+__device__ __forceinline__ int first_record(const int* hdr, int place, int b) {
+    return b > 0 && place < hdr[kOrderRecorded] ? (int)((unsigned)hdr[kOrderSlots + b] + (unsigned)place * (unsigned)b)
+                                                : -1;
 }
 
 // Each block reserves a range per batch count for its rays (one global
 // atomic per count), then places them there (order within a count is
 // arbitrary).
 __global__ __launch_bounds__(256) void k_order_scatter(const int32_t* __restrict__ n_eval, int64_t n, int64_t chunk,
-                                                       int nbins, int* __restrict__ hdr, int32_t* __restrict__ order) {
+                                                       int nbins, int* __restrict__ hdr, int32_t* __restrict__ order,
+                                                       int32_t* __restrict__ slot_of_ray) {
     __shared__ int cnt[kOrderBins], base[kOrderBins];
     for (int i = threadIdx.x; i < nbins; i += 256) cnt[i] = 0;
     __syncthreads();
@@ -289,7 +319,9 @@ __global__ __launch_bounds__(256) void k_order_scatter(const int32_t* __restrict
     __syncthreads();
     for (int64_t r = s + threadIdx.x; r < e; r += 256) {
         const int bb = batch_bin(n_eval[r], nbins);
-        order[base[bb] + atomicAdd(&cnt[bb], 1)] = (int32_t)r;
+        const int place = base[bb] + atomicAdd(&cnt[bb], 1);
+        order[place] = (int32_t)r;
+        if (slot_of_ray) slot_of_ray[r] = first_record(hdr, place, bb);
     }
 }
 
@@ -320,6 +352,7 @@ __global__ __launch_bounds__(kOrderSmallThreads) void k_order_small(const int32_
     }
     if (t < kOrderBins) hdr[t] = t < nbins ? cnt[t] : 0;
     if (t == kOrderBins) hdr[kOrderCounter] = 0;
+    if (t == kOrderBins + 1) hdr[kOrderRecorded] = 0;
     __syncthreads();
     for (int r = t; r < n; r += kOrderSmallThreads) order[atomicAdd(&next[batch_bin(n_eval[r], nbins)], 1)] = r;
 }
@@ -470,7 +503,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
             gt[0] = (Tnext * msoft * gv - suffix - Tn * gT) * rp.delta * tau;
 #pragma unroll
             for (int c = 0; c < 7; ++c) gt[c + 1] = w * g7[c] * v[c] * (1.0f - v[c]);
-            scatter_batch_runs(scene_argument(), gV, gxy, gxz, gyz, stage, act, cn, gt, gl, lane);
+            scatter_batch_runs<true>(scene_argument(), gV, gxy, gxz, gyz, stage, act, cn, gt, gl, lane);
             if (kSoft && gocc) scatter_occ(gocc, act, oc, w0 * gv, gl, lane);  // dL/dM = w0 (g7 . v)
             carry += __shfl(incl, kGroup - 1, kGroup);
             done += nb_eff;
@@ -479,30 +512,143 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
         });
     };
     // Rays without samples, last in the order, are not handed out.
-    hand_out(next_ray, 0, n - sched[0], gid, lane, [&](int64_t idx) { ray_body(order[idx]); });
+    hand_out(next_ray, sched[kOrderRecorded], n - sched[0], gid, lane, [&](int64_t idx) { ray_body(order[idx]); });
+}
+
+// ---------------------------------------------------------------------------
+// The same gradients from the forward's records (BatchRecords): no placement,
+// no gather.  A ray's batches are taken last first, so that the suffix S_i
+// grows by their totals; the optical depth in front of a batch is the
+// forward's own.  dL/dt replaces the activations in the record, for the XZ and
+// YZ sums by tiles (bwd_tiles.hip); the grid and XY are scattered here.  The
+// next batch's record is loaded while one is scattered.
+//
+// Bound by the scatter's float atomics: 82 million 64-byte requests of 2^18
+// rays in float32 in 4.5 ms, near the 20.6 G/s that they reach beyond L2
+//.  The step took 12.3 ms with
+// the samples replayed and four sources scattered; the forward with records
+// (3.3), the counts ahead of it (0.25), this and the tiles' sums take 11.1.
+// ---------------------------------------------------------------------------
+struct RecordLoad {
+    float a, v[7], px, py, pz, carry;
+};
+
+__device__ __forceinline__ RecordLoad load_record(const float* __restrict__ r, int gl) {
+    RecordLoad l;
+    const float* own = r + record_place(gl);
+    l.a = own[0];
+#pragma unroll
+    for (int c = 0; c < 7; ++c) l.v[c] = own[(c + 1) * kGroup];
+    l.px = r[kRecPoint + gl];
+    l.py = r[kRecPoint + kGroup + gl];
+    l.pz = r[kRecPoint + 2 * kGroup + gl];
+    l.carry = r[kRecCarry];
+    return l;
+}
+
+template <bool kSoft>
+__global__ __launch_bounds__(kBlock, 5) void k_grad(SceneDev sc, RayParams rp, const int32_t* __restrict__ order,
+                                                    const int* __restrict__ sched, unsigned int* __restrict__ next_ray,
+                                                    BatchRecords br, const float* __restrict__ Ts,
+                                                    const int32_t* __restrict__ n_eval, const float* __restrict__ G8,
+                                                    float* __restrict__ gV, float* __restrict__ gxy,
+                                                    float* __restrict__ gocc) {
+    __shared__ __attribute__((aligned(16))) Stage stages[kGroupsPerBlock];
+    const int lane = threadIdx.x & 63;
+    const int gl = lane & (kGroup - 1);
+    const int gid = threadIdx.x / kGroup;
+    Stage& stage = stages[gid];
+    auto ray_body = [&](int64_t idx) {
+        const int64_t ray = order[idx];
+        const int ne = n_eval[ray];
+        if (ne <= 0) return;
+        float* rec = br.rec + (size_t)br.slot_of_ray[ray] * kRecFloats;
+        const float Tn = Ts[ray];
+        const float4 ga = *reinterpret_cast<const float4*>(G8 + ray * 8);
+        const float4 gb = *reinterpret_cast<const float4*>(G8 + ray * 8 + 4);
+        const float g7[7] = {ga.x, ga.y, ga.z, ga.w, gb.x, gb.y, gb.z};
+        const float gTn = Tn * gb.w;
+        float after = 0.0f;  // w (g7 . v) of the later batches
+        int b = (ne - 1) / kGroup;
+        RecordLoad nx = load_record(rec + (size_t)b * kRecFloats, gl);
+        for (; b >= 0; --b) {
+            const RecordLoad l = nx;
+            if (b > 0) nx = load_record(rec + (size_t)(b - 1) * kRecFloats, gl);
+            const bool act = gl < ne - b * kGroup;
+            const float a = act ? l.a : 0.0f;
+            float v[7];
+#pragma unroll
+            for (int c = 0; c < 7; ++c) v[c] = act ? l.v[c] : 0.0f;
+            const float3 p = make_float3(l.px, l.py, l.pz);
+            const float incl = g_scan_incl(a, gl);
+            const float Ti = __expf(-(l.carry + g_shift_up1(incl)));
+            const float Tnext = __expf(-(l.carry + incl));
+            const float w0 = act ? Ti * (-expm1f(-a)) : 0.0f;  // Eq. 1 weight
+            OccValue oc{1.0f, 0.0f, 0.0f, -1};
+            if (kSoft && act) oc = occ_value(scene_argument(), p, rp.occ_inv_eps);
+            const float msoft = kSoft ? oc.m : 1.0f;  // Eq. 8 scales the weight, not T
+            const float w = w0 * msoft;
+            float gv = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 7; ++c) gv += g7[c] * v[c];
+            const float later = g_rscan_incl(w * gv, gl);
+            const float suffix = g_shift_down1(later) + after;
+            after += row_bcast<0>(later);
+            float gt[8];
+            gt[0] = act ? (Tnext * msoft * gv - suffix - gTn) * a : 0.0f;
+#pragma unroll
+            for (int c = 0; c < 7; ++c) gt[c + 1] = w * g7[c] * v[c] * (1.0f - v[c]);
+            float* r = rec + (size_t)b * kRecFloats + gl;
+            bool add = false;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                r[c * kGroup] = gt[c];
+                add |= gt[c] != 0.0f;
+            }
+            if (!(add && act)) r[kRecPoint] = __uint_as_float(0x7fc00000u);
+            Corners cn{};  // defined keys and weights on inactive lanes, which the group scans read
+            if (act) cn = corners_of(scene_argument(), p);
+            scatter_batch_runs<false>(scene_argument(), gV, gxy, nullptr, nullptr, stage, act, cn, gt, gl, lane);
+            if (kSoft && gocc) scatter_occ(gocc, act, oc, w0 * gv, gl, lane);  // dL/dM = w0 (g7 . v)
+        }
+    };
+    hand_out(next_ray, 0, sched[kOrderRecorded], gid, lane, ray_body);
+}
+
+hipError_t launch_bwd_order(const int32_t* counts, int64_t n, int n_max, int32_t* order, int* sched,
+                            const BatchRecords* br, hipStream_t s) {
+    const int nbins = (n_max + kGroup - 1) / kGroup + 1, cap = br ? br->cap : 0;
+    int32_t* slots = br ? br->slot_of_ray : nullptr;
+    static_assert(kOrderSmall * (OM_MAX_SAMPLES / kGroup) <= kRecordBatches, "the small order places no records");
+    if (n <= kOrderSmall) {
+        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(kOrderSmallThreads), 0, s, counts, (int)n, nbins, sched, order);
+        return hipGetLastError();
+    }
+    const int64_t sort_blocks = min((n + 4095) / 4096, (int64_t)1024);
+    const int64_t sort_chunk = (n + sort_blocks - 1) / sort_blocks;
+    hipLaunchKernelGGL(k_order_clear, dim3(1), dim3(64), 0, s, sched);
+    hipLaunchKernelGGL(k_order_hist, dim3((unsigned)sort_blocks), dim3(256), 0, s, counts, n, sort_chunk, nbins, sched);
+    hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(64), 0, s, nbins, cap, sched);
+    hipLaunchKernelGGL(k_order_scatter, dim3((unsigned)sort_blocks), dim3(256), 0, s, counts, n, sort_chunk, nbins,
+                       sched, order, slots);
+    return hipGetLastError();
 }
 
 hipError_t launch_march_bwd(const SceneDev& sc, bool bf16, const RayParams& rp, const float* o, const float* d,
                             int64_t n, const float* T, const int32_t* n_eval, const float* batch_wv, const float* G8,
-                            int32_t* order, int* sched, float* gV, float* gxy, float* gxz, float* gyz, float* gocc,
-                            hipStream_t s) {
-    // Longest-first order (counting sort by batch count), then persistent
-    // blocks, as many as the chip holds (4 waves per SIMD).
-    const int nbins = (rp.n_max + kGroup - 1) / kGroup + 1;
-    const int64_t sort_blocks = min((n + 4095) / 4096, (int64_t)1024);
-    const int64_t sort_chunk = (n + sort_blocks - 1) / sort_blocks;
-    if (n <= kOrderSmall) {
-        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(kOrderSmallThreads), 0, s, n_eval, (int)n, nbins, sched, order);
-    } else {
-        hipLaunchKernelGGL(k_order_clear, dim3(1), dim3(64), 0, s, sched);
-        hipLaunchKernelGGL(k_order_hist, dim3((unsigned)sort_blocks), dim3(256), 0, s, n_eval, n, sort_chunk, nbins,
-                           sched);
-        hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(64), 0, s, nbins, sched);
-        hipLaunchKernelGGL(k_order_scatter, dim3((unsigned)sort_blocks), dim3(256), 0, s, n_eval, n, sort_chunk, nbins,
-                           sched, order);
-    }
+                            const int32_t* order, int* sched, const BatchRecords* br, float* gV, float* gxy,
+                            float* gxz, float* gyz, float* gocc, hipStream_t s) {
+    // Persistent blocks, as many as the chip holds: 4 waves per SIMD replay, 5
+    // go through records (their launch bounds).
     unsigned int* next_ray = reinterpret_cast<unsigned int*>(sched + kOrderCounter);
-    const dim3 grid((unsigned)min((n + kGroupsPerBlock - 1) / kGroupsPerBlock, (int64_t)(256 * 4))), block(kBlock);
+    const int64_t blocks = (n + kGroupsPerBlock - 1) / kGroupsPerBlock;
+    const dim3 grid((unsigned)min(blocks, (int64_t)(256 * 4))), grad_grid((unsigned)min(blocks, (int64_t)(256 * 5)));
+    const dim3 block(kBlock);
+    const bool soft = rp.occ_inv_eps > 0.0f;
+    if (br) {
+        hipLaunchKernelGGL(soft ? k_grad<true> : k_grad<false>, grad_grid, block, 0, s, sc, rp, order, sched, next_ray + 1,
+                           *br, T, n_eval, G8, gV, gxy, gocc);
+    }
     typedef void (*Form)(SceneDev, RayParams, const float*, const float*, int64_t, const int32_t*, const int*,
                          unsigned int*, const float*, const int32_t*, const float*, const float*, float*, float*,
                          float*, float*, float*);
@@ -511,8 +657,8 @@ hipError_t launch_march_bwd(const SceneDev& sc, bool bf16, const RayParams& rp, 
          {k_march_bwd<F32Store, true, false>, k_march_bwd<F32Store, true, true>}},
         {{k_march_bwd<BF16Store, false, false>, k_march_bwd<BF16Store, false, true>},
          {k_march_bwd<BF16Store, true, false>, k_march_bwd<BF16Store, true, true>}}};
-    hipLaunchKernelGGL(forms[bf16][rp.occ_inv_eps > 0.0f][narrow_scene(sc, bf16 ? OM_BF16 : OM_F32)], grid, block, 0, s,
-                       sc, rp, o, d, n, order, sched, next_ray, T, n_eval, batch_wv, G8, gV, gxy, gxz, gyz, gocc);
+    hipLaunchKernelGGL(forms[bf16][soft][narrow_scene(sc, bf16 ? OM_BF16 : OM_F32)], grid, block, 0, s, sc, rp, o, d, n,
+                       order, sched, next_ray, T, n_eval, batch_wv, G8, gV, gxy, gxz, gyz, gocc);
     return hipGetLastError();
 }
 

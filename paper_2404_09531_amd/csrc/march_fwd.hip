@@ -39,6 +39,32 @@ __global__ __launch_bounds__(kBlock) void k_place(SceneDev sc, RayParams rp, con
     if (gl == 0) n_placed[ray] = cnt;
 }
 
+// The counts alone, ahead of a training step that gives every batch a record.
+__global__ __launch_bounds__(kBlock) void k_count(SceneDev sc, RayParams rp, const float* __restrict__ o_,
+                                                  const float* __restrict__ d_, int64_t n,
+                                                  int32_t* __restrict__ n_placed) {
+    __shared__ int qs[kGroupsPerBlock][kQueue];
+    const int lane = threadIdx.x & 63;
+    const int gl = lane & (kGroup - 1);
+    const int gid = threadIdx.x / kGroup;
+    const int64_t ray = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGroupsPerBlock + gid;
+    if (ray >= n) return;
+    const int cnt = march_candidates(sc, rp, load3(o_, ray), load3(d_, ray), qs[gid], gl, gl, lane,
+                                     [](int, int) { return false; });
+    if (gl == 0) n_placed[ray] = cnt;
+}
+
+// What a forward leaves for the backward: nothing, the per-batch sums of w v,
+// or a record per batch (the sums for rays without records).
+enum { kSaveNone, kSaveSums, kSaveRecords };
+
+// Marks the ray's records from `batch` on, which it did not reach (early
+// termination), as without samples.
+__device__ __forceinline__ void clear_records(const BatchRecords& br, int slot, int batch, int slots, int gl) {
+    for (; batch < slots; ++batch)
+        br.rec[(size_t)(slot + batch) * kRecFloats + kRecPoint + gl] = __uint_as_float(0x7fc00000u);
+}
+
 // ---------------------------------------------------------------------------
 // Rows read by a render: for every evaluated sample (the first n_eval placed
 // samples of the ray, or all placed samples without n_eval), a byte 1 is
@@ -128,14 +154,14 @@ struct GatherBF16 {
 // Waves per SIMD the one-lane-per-sample forwards are compiled for: without
 // the soft occupancy and with 32-bit addresses they fit 6 (<= 80 VGPRs)
 // without spilling; the other forms keep the compiler's choice.
-template <class Gather, bool kSoft, bool kNarrow>
-constexpr int lane_min_waves() { return !kSoft && kNarrow ? 6 : 1; }
+template <class Gather, int kSave, bool kSoft, bool kNarrow>
+constexpr int lane_min_waves() { return !kSoft && kNarrow ? (kSave == kSaveRecords ? 5 : 6) : 1; }
 
-template <class Gather, bool kBW, bool kSoft, bool kSparse, bool kNarrow>
-__global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSoft, kNarrow>())) void k_march_fwd_lane(
+template <class Gather, int kSave, bool kSoft, bool kSparse, bool kNarrow>
+__global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarrow>())) void k_march_fwd_lane(
     SceneDev sc, RayParams rp, const float* __restrict__ o_, const float* __restrict__ d_, int64_t n,
     float* __restrict__ F, float* __restrict__ T, int32_t* __restrict__ n_placed, int32_t* __restrict__ n_eval,
-    float* __restrict__ BW) {
+    float* __restrict__ BW, BatchRecords br) {
     __shared__ int qs[kGroupsPerBlock][kQueue];
     const int lane = threadIdx.x & 63;
     const int gl = lane & (kGroup - 1);
@@ -149,6 +175,8 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSoft, kNarrow>()))
     float carry = 0.0f;
     int evals = 0, batch = 0;
     const int slots = (rp.n_max + kGroup - 1) / kGroup;
+    const int slot = kSave == kSaveRecords ? br.slot_of_ray[ray] : -1;
+    const int alloc = kSave == kSaveRecords ? (n_placed[ray] + kGroup - 1) / kGroup : 0;
     const int placed = march_candidates(sc, rp, o, d, qs[gid], gl, gl, lane, [&](int kq, int nb) {
         const bool act = gl < nb;
         float t[8];
@@ -187,7 +215,18 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSoft, kNarrow>()))
         if (gl >= nb_eff) w = 0.0f;
 #pragma unroll
         for (int c = 0; c < 7; ++c) acc[c] += w * v[c];
-        if (kBW) {
+        if (kSave == kSaveRecords && slot >= 0) {
+            float* r = br.rec + (size_t)(slot + batch) * kRecFloats;
+            float* own = r + record_place(gl);
+            own[0] = a;
+#pragma unroll
+            for (int c = 0; c < 7; ++c) own[(c + 1) * kGroup] = v[c];
+            const float3 p = lattice_point(kq, o, d, rp.delta);
+            r[kRecPoint + gl] = p.x;
+            r[kRecPoint + kGroup + gl] = p.y;
+            r[kRecPoint + 2 * kGroup + gl] = p.z;
+            if (gl == 0) r[kRecCarry] = carry;
+        } else if (kSave != kSaveNone) {
             float* dst = BW + ((size_t)ray * slots + batch) * 7;
 #pragma unroll
             for (int c = 0; c < 7; ++c) store_group_total(w * v[c], gl, dst + c);
@@ -197,6 +236,7 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSoft, kNarrow>()))
         ++batch;
         return stop;
     });
+    if (kSave == kSaveRecords && slot >= 0) clear_records(br, slot, batch, alloc, gl);
     float f[7];
 #pragma unroll
     for (int c = 0; c < 7; ++c) f[c] = g_sum(acc[c]);
@@ -278,11 +318,11 @@ __device__ __forceinline__ void quad_gather(const SceneDev& sc, const QuadSample
     }
 }
 
-template <bool kBW, bool kSoft, bool kSparse, bool kNarrow>
+template <int kSave, bool kSoft, bool kSparse, bool kNarrow>
 __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
     SceneDev sc, RayParams rp, const float* __restrict__ o_, const float* __restrict__ d_, int64_t n,
     float* __restrict__ F, float* __restrict__ T, int32_t* __restrict__ n_placed, int32_t* __restrict__ n_eval,
-    float* __restrict__ BW) {
+    float* __restrict__ BW, BatchRecords br) {
     __shared__ int qs[kGroupsPerBlock][kQueue];
     const int lane = threadIdx.x & 63;
     const int gl = lane & (kGroup - 1);
@@ -298,6 +338,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
     float carry = 0.0f;
     int evals = 0, batch = 0;
     const int slots = (rp.n_max + kGroup - 1) / kGroup;
+    const int slot = kSave == kSaveRecords ? br.slot_of_ray[ray] : -1;
+    const int alloc = kSave == kSaveRecords ? (n_placed[ray] + kGroup - 1) / kGroup : 0;
     const int placed = march_candidates(sc, rp, o, d, qs[gid], gl, pos, lane, [&](int kq, int nb) {
         QuadSample own;
         {
@@ -360,7 +402,20 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
         b1 += quad_bcast<3>(w) * v1[3];
         acc0 += b0;
         acc1 += b1;
-        if (kBW) {
+        if (kSave == kSaveRecords && slot >= 0) {
+            float* r = br.rec + (size_t)(slot + batch) * kRecFloats;
+            float4* rows = reinterpret_cast<float4*>(r + 2 * q * kGroup + (gl & ~3));  // the quad's four samples
+            const float4 depth = make_float4(quad_bcast<0>(a), quad_bcast<1>(a), quad_bcast<2>(a), quad_bcast<3>(a));
+            rows[0] = q == 0 ? depth : make_float4(v0[0], v0[1], v0[2], v0[3]);
+            rows[kGroup / 4] = make_float4(v1[0], v1[1], v1[2], v1[3]);
+            int kr = kq;  // the point is formed again, not held across the gather
+            asm volatile("" : "+v"(kr));
+            const float3 p = lattice_point(kr, o, d, rp.delta);
+            r[kRecPoint + pos] = p.x;
+            r[kRecPoint + kGroup + pos] = p.y;
+            r[kRecPoint + 2 * kGroup + pos] = p.z;
+            if (gl == 0) r[kRecCarry] = carry;
+        } else if (kSave != kSaveNone) {
             b0 = quad_column_sum(b0);
             b1 = quad_column_sum(b1);
             float* dst = BW + ((size_t)ray * slots + batch) * 7 + 2 * gl;
@@ -376,6 +431,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
         evals += nb_eff;
         return stop;
     });
+    if (kSave == kSaveRecords && slot >= 0) clear_records(br, slot, batch, alloc, gl);
     acc0 = quad_column_sum(acc0);
     acc1 = quad_column_sum(acc1);
     if (gl < 4) {
@@ -394,6 +450,12 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
 // Launchers.
 // ---------------------------------------------------------------------------
 static inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kGroupsPerBlock - 1) / kGroupsPerBlock); }
+
+hipError_t launch_count(const SceneDev& sc, const RayParams& rp, const float* o, const float* d, int64_t n,
+                        int32_t* n_placed, hipStream_t s) {
+    hipLaunchKernelGGL(k_count, dim3(blocks_for(n)), dim3(kBlock), 0, s, sc, rp, o, d, n, n_placed);
+    return hipGetLastError();
+}
 
 hipError_t launch_place(const SceneDev& sc, const RayParams& rp, const float* o, const float* d, int64_t n,
                         int32_t* k_out, int32_t* n_placed, hipStream_t s) {
@@ -428,45 +490,39 @@ bool narrow_scene(const SceneDev& sc, int dtype) {
 template <bool kSoft, bool kSparse, bool kNarrow>
 static void launch_fwd_form(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
                             int64_t n, float* F, float* T, int32_t* n_placed, int32_t* n_eval, float* batch_wv,
-                            hipStream_t s) {
-    const dim3 grid(blocks_for(n)), block(kBlock);
+                            const BatchRecords* br, hipStream_t s) {
     // Sparse blocks and 8-bit features are render only (the API refuses
     // per-batch sums for them).
-    constexpr bool kSums = !kSparse;
-    if (dtype == OM_U8) {
-        hipLaunchKernelGGL((k_march_fwd_lane<GatherU8, false, kSoft, kSparse, kNarrow>), grid, block, 0, s, sc, rp, o,
-                           d, n, F, T, n_placed, n_eval, nullptr);
-    } else if (dtype == OM_BF16) {
-        if (kSums && batch_wv)
-            hipLaunchKernelGGL((k_march_fwd_lane<GatherBF16, kSums, kSoft, kSparse, kNarrow>), grid, block, 0, s, sc,
-                               rp, o, d, n, F, T, n_placed, n_eval, batch_wv);
-        else
-            hipLaunchKernelGGL((k_march_fwd_lane<GatherBF16, false, kSoft, kSparse, kNarrow>), grid, block, 0, s, sc,
-                               rp, o, d, n, F, T, n_placed, n_eval, nullptr);
-    } else {
-        if (kSums && batch_wv)
-            hipLaunchKernelGGL((k_march_fwd_f32q<kSums, kSoft, kSparse, kNarrow>), grid, block, 0, s, sc, rp, o, d, n,
-                               F, T, n_placed, n_eval, batch_wv);
-        else
-            hipLaunchKernelGGL((k_march_fwd_f32q<false, kSoft, kSparse, kNarrow>), grid, block, 0, s, sc, rp, o, d, n,
-                               F, T, n_placed, n_eval, nullptr);
-    }
+    constexpr int kSums = kSparse ? kSaveNone : kSaveSums, kRecs = kSparse ? kSaveNone : kSaveRecords;
+    typedef void (*Kernel)(SceneDev, RayParams, const float*, const float*, int64_t, float*, float*, int32_t*,
+                           int32_t*, float*, BatchRecords);
+    static constexpr Kernel f32[3] = {k_march_fwd_f32q<kSaveNone, kSoft, kSparse, kNarrow>,
+                                      k_march_fwd_f32q<kSums, kSoft, kSparse, kNarrow>,
+                                      k_march_fwd_f32q<kRecs, kSoft, kSparse, kNarrow>};
+    static constexpr Kernel bf16[3] = {k_march_fwd_lane<GatherBF16, kSaveNone, kSoft, kSparse, kNarrow>,
+                                       k_march_fwd_lane<GatherBF16, kSums, kSoft, kSparse, kNarrow>,
+                                       k_march_fwd_lane<GatherBF16, kRecs, kSoft, kSparse, kNarrow>};
+    const int save = br ? kSaveRecords : batch_wv ? kSaveSums : kSaveNone;
+    const Kernel k = dtype == OM_U8 ? k_march_fwd_lane<GatherU8, kSaveNone, kSoft, kSparse, kNarrow>
+                                    : dtype == OM_BF16 ? bf16[save] : f32[save];
+    hipLaunchKernelGGL(k, dim3(blocks_for(n)), dim3(kBlock), 0, s, sc, rp, o, d, n, F, T, n_placed, n_eval, batch_wv,
+                       br ? *br : BatchRecords{});
 }
 
 hipError_t launch_march_fwd(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
                             int64_t n, float* F, float* T, int32_t* n_placed, int32_t* n_eval, float* batch_wv,
-                            hipStream_t s) {
+                            const BatchRecords* br, hipStream_t s) {
     // The per-batch sums, the soft occupancy, the sparse blocks and the wide
     // addresses are separate specialisations, so the plain path carries none.
     typedef void (*Form)(const SceneDev&, int, const RayParams&, const float*, const float*, int64_t, float*, float*,
-                         int32_t*, int32_t*, float*, hipStream_t);
+                         int32_t*, int32_t*, float*, const BatchRecords*, hipStream_t);
     static constexpr Form forms[2][2][2] = {
         {{launch_fwd_form<false, false, false>, launch_fwd_form<false, false, true>},
          {launch_fwd_form<false, true, false>, launch_fwd_form<false, true, true>}},
         {{launch_fwd_form<true, false, false>, launch_fwd_form<true, false, true>},
          {launch_fwd_form<true, true, false>, launch_fwd_form<true, true, true>}}};
     forms[rp.occ_inv_eps > 0.0f][sc.blk_shift > 0][narrow_scene(sc, dtype)](sc, dtype, rp, o, d, n, F, T, n_placed,
-                                                                           n_eval, batch_wv, s);
+                                                                           n_eval, batch_wv, br, s);
     return hipGetLastError();
 }
 

@@ -15,16 +15,73 @@ hipError_t launch_place(const SceneDev& sc, const RayParams& rp, const float* o,
                         int32_t* k_out, int32_t* n_placed, hipStream_t s);
 hipError_t launch_mark(const SceneDev& sc, const RayParams& rp, const float* o, const float* d, int64_t n,
                        const int32_t* n_eval, uint8_t* fg, uint8_t* fxy, uint8_t* fxz, uint8_t* fyz, hipStream_t s);
+// Batch records of a training step (float32 [slots][kRecFloats]): the forward
+// leaves one per 16-sample batch of a ray, and the backward works from them
+// instead of replaying the samples.
+//   [0, 128)    [8][16]: channel 0 the samples' optical depths, 1..7 their
+//               activated features, from the forward in record_place order;
+//               then dL/dt of the 8 channels, in sample order, from k_grad
+//   [128, 176)  [3][16]: the sample points (x NaN: nothing to add)
+//   176         the optical depth in front of the batch
+constexpr int kRecPoint = 8 * kGroup, kRecCarry = 11 * kGroup, kRecFloats = 12 * kGroup;
+// A fused step keeps records where n rays of at most n_max samples may have
+// more than kRecordBatches batches and the placement counts find at least
+// kRecordMin.  Steps with and without them: 423,000 batches (of 524,288)
+// 1.81 and 1.77 ms, 637,000 (of 2^20) 3.32 and 3.43, 2.54 million 11.2 and
+// 12.3, 5.1 million in bfloat16 20.7 and 23.0; below, the planes' tiles are
+// too thinly covered to pay for their sums (212,000: 1.15 and 1.06).
+constexpr int64_t kRecordBatches = 1 << 20, kRecordMin = 1 << 19;
+struct BatchRecords {
+    float* rec;
+    int32_t* slot_of_ray;  // [n] first record of each ray, -1: none
+    int cap;               // records
+};
+// Where sample i of a batch stands in a channel row as the forward writes it:
+// the lane that holds it in the float32 forward.
+__host__ __device__ constexpr int record_place(int i) { return 4 * (i & 3) + (i >> 2); }
+
+// br: NULL, or the records; rays without one get the per-batch sums.
+// n_placed then holds the placement counts on entry (launch_count).
 hipError_t launch_march_fwd(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
                             int64_t n, float* F, float* T, int32_t* n_placed, int32_t* n_eval, float* batch_wv,
-                            hipStream_t s);
+                            const BatchRecords* br, hipStream_t s);
+// Samples placed per ray.
+hipError_t launch_count(const SceneDev& sc, const RayParams& rp, const float* o, const float* d, int64_t n,
+                        int32_t* n_placed, hipStream_t s);
 // Scheduling words (int32) of the march backward in its workspace: the
-// ray-order histogram, its cursors and the hand-out counter.
+// ray-order histogram, its cursors and the hand-out counters, and the slots of
+// the rays' records.
 constexpr int kBwdSchedWords = 256;
+constexpr int kOrderRecords = 198;  // records in use
+
+// Longest-first order of the rays by `counts`; with br, also their records
+// (br->slot_of_ray), handed out to whole rays in that order.
+hipError_t launch_bwd_order(const int32_t* counts, int64_t n, int n_max, int32_t* order, int* sched,
+                            const BatchRecords* br, hipStream_t s);
+// The march backward over that order; br: the rays with records go through
+// them, the others replay their samples.
 hipError_t launch_march_bwd(const SceneDev& sc, bool bf16, const RayParams& rp, const float* o, const float* d,
                             int64_t n, const float* T, const int32_t* n_eval, const float* batch_wv, const float* G8,
-                            int32_t* order, int* sched, float* gV, float* gxy, float* gxz, float* gyz, float* gocc,
-                            hipStream_t s);
+                            const int32_t* order, int* sched, const BatchRecords* br, float* gV, float* gxy,
+                            float* gxz, float* gyz, float* gocc, hipStream_t s);
+
+// Sums of the recorded XZ and YZ gradients (bwd_tiles.hip).
+constexpr int kTileU = 17, kTileV = 20;  // base texels per tile
+constexpr int kTileKeys = 4;             // tiles a batch may be listed under, per plane
+constexpr int kNoTile = 0xffff;
+struct TileLists {
+    uint16_t* keys;   // [cap][2 kTileKeys]: the tile ids of a batch on XZ and YZ
+    int32_t* listed;  // [2 kTileKeys cap]: records by tile
+    int* bins;        // [nbins] entries per tile, then [nbins] cursors (in the end: where each tile's list ends)
+    int* total;       // entries
+    int nbins, yz;    // tiles, and the first of YZ
+    int nu_x, nu_y;   // tiles per row of XZ and of YZ
+};
+// Workspace bytes of the records and lists for n rays of at most n_max
+// samples, or 0 where they do not pay; fills *br and *tl when base is non-NULL.
+int64_t record_workspace(const SceneDev& sc, int64_t n, int n_max, void* base, BatchRecords* br, TileLists* tl);
+hipError_t launch_tile_sums(const SceneDev& sc, const BatchRecords& br, const TileLists& tl, const int* records,
+                            float* gxz, float* gyz, hipStream_t s);
 hipError_t launch_mlp_bwd(const float* W, int mlp_in, const RayParams& rp, const float* F, const float* d,
                           const int32_t* n_eval, const float* dC, const float* dF, int64_t n, float* G8, float* gmlp,
                           hipStream_t s);

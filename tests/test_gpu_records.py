@@ -1,0 +1,174 @@
+"""GPU: the fused step of a large batch through its batch records and tile
+sums, against the same step in the smallest workspace, which replays.
+
+Records are kept from 2^20 possible and 2^19 placed batches on, 6 x 2^20 of
+them at most; the XZ and YZ gradients are summed in tiles of 17 x 20 base
+texels, of which a batch is listed under four per plane.  The planes below end
+at a tile's edge, one texel behind it, and inside the first tile.
+
+Bar: counts equal; C, F and T, whose arithmetic is the same up to the
+compiler's choice of fused multiply-adds, within the 1e-5 that each is held to
+against the oracle; the gradients are the same float32 terms in another order,
+the floor of test_backward_large_batch_equals_its_halves.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2404_09531_amd as om
+import scenegen
+from tests._scenes import micro_scene
+from tests.gpu_util import DEV, log, rays_to, upload_scene
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("grid", "plane_xy", "plane_xz", "plane_yz", "mlp")
+BG = (0.25, 0.5, 0.75)
+
+
+class Step:
+    """A fused step of one batch and its buffers."""
+
+    def __init__(self, sc, o, d, dtype=torch.float32, occ=False, **kw):
+        self.scene, self.t = upload_scene(sc, dtype)
+        self.o, self.d = rays_to(o, d)
+        self.n, self.kw, self.occ = len(o), dict(c_bg=BG, **kw), occ
+        g = torch.Generator(device=DEV)
+        g.manual_seed(7)
+        self.target = torch.rand(self.n, 3, device=DEV, generator=g)
+        self.need = om.fwd_bwd_l2_workspace_size(self.n, kw["n_max"])
+        self.records = om.fwd_bwd_l2_records_size(self.scene, self.n, kw["n_max"])
+
+    def buffers(self):
+        e = lambda *s, dt=torch.float32: torch.empty(s, dtype=dt, device=DEV)  # noqa: E731
+        out = dict(C=e(self.n, 3), T=e(self.n), F=e(self.n, 7), n_placed=e(self.n, dt=torch.int32),
+                   n_eval=e(self.n, dt=torch.int32))
+        keys = KEYS + (("occ",) if self.occ else ())
+        return out, {k: torch.zeros(self.t[k].shape, device=DEV) for k in keys}, e(1)
+
+    def run(self, out, grads, loss, nbytes):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+        om.render_fwd_bwd_l2(self.scene, self.o, self.d, self.target, out, grads, loss=loss, workspace=ws, **self.kw)
+
+    def both(self):
+        got = []
+        for nbytes in (self.need, self.need + self.records):
+            got.append(self.buffers())
+            self.run(*got[-1], nbytes)
+        return got
+
+
+def assert_same(plain, recorded):
+    for k in ("n_placed", "n_eval"):
+        assert torch.equal(plain[0][k], recorded[0][k]), k
+    for k in ("C", "F", "T"):
+        assert float((plain[0][k] - recorded[0][k]).abs().max()) <= 1e-5, k
+    assert float((plain[2] - recorded[2]).abs()) <= 1e-5
+    assert_grads(plain[1], recorded[1])
+
+
+def assert_grads(a, b):
+    for k in a:
+        scale = float(a[k].abs().max())
+        assert scale > 0, k
+        assert float(((a[k] - b[k]).abs() - (1e-3 * a[k].abs() + 5e-5 * scale)).max()) <= 0, k
+
+
+def oblique(n):
+    return scenegen.oblique_rays(n, seed=n)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("t_term,occ_eps", [(0.0, 0.0), (1e-2, 0.0), (0.0, 0.02), (1e-2, 0.02)])
+def test_forms(dtype, t_term, occ_eps):
+    log(f"test_forms: {dtype}, t_term {t_term}, occ_eps {occ_eps}")
+    sc = micro_scene(grid=(20, 18, 9), planes=(40, 30, 45), m=8, zmin=0.01, zmax=0.24, seed=5)
+    s = Step(sc, *oblique(70001), dtype=dtype, occ=occ_eps > 0, n_max=256, t_term=t_term, occ_eps=occ_eps)
+    assert s.records > 0
+    assert_same(*s.both())
+
+
+@pytest.mark.parametrize("planes", [(2, 2, 2), (18, 35, 21), (19, 36, 22), (35, 52, 41), (300, 17, 64)])
+def test_tile_edges(planes):
+    log(f"test_tile_edges: planes {planes}")
+    s = Step(micro_scene(grid=(5, 6, 3), planes=planes, m=4, seed=6), *oblique(66003), n_max=256)
+    assert s.records > 0
+    assert_same(*s.both())
+
+
+def test_batches_across_many_tiles():
+    """Long steps across finely divided planes: ten tiles per batch."""
+    log("test_batches_across_many_tiles")
+    n = 100001
+    rng = np.random.default_rng(4)
+    o = np.stack([np.full(n, -1.1), rng.uniform(-0.8, 0.8, n), rng.uniform(0.02, 0.2, n)], 1).astype(np.float32)
+    d = np.stack([np.ones(n), rng.uniform(-0.2, 0.2, n), rng.uniform(-0.02, 0.02, n)], 1)
+    d = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    sc = micro_scene(grid=(5, 6, 3), planes=(1000, 900, 130), m=4, seed=6)
+    s = Step(sc, o, d, n_max=256, delta=2.0 ** -6)
+    assert s.records > 0
+    plain, recorded = s.both()
+    assert int(((plain[0]["n_placed"] + 15) // 16).sum()) >= 1 << 19
+    assert_same(plain, recorded)
+
+
+@pytest.mark.parametrize("n,zmax", [(70001, 0.02), ((1 << 20) + 3, 0.25)])
+def test_few_batches_and_more_than_the_records(n, zmax):
+    log(f"test_few_batches_and_more_than_the_records: {n} rays, occupied up to {zmax}")
+    s = Step(micro_scene(grid=(20, 18, 9), planes=(40, 30, 45), m=8, zmax=zmax, seed=5), *oblique(n), n_max=256)
+    assert s.records > 0
+    plain, recorded = s.both()
+    batches = int(((plain[0]["n_placed"] + 15) // 16).sum())
+    assert batches < 1 << 19 if zmax < 0.1 else batches > 6 << 20
+    assert_same(plain, recorded)
+
+
+def test_workspace_rules():
+    """One byte less than the records need is the smallest workspace's step;
+    no workspace takes the records; small batches have none."""
+    log("test_workspace_rules")
+    sc = micro_scene(grid=(20, 18, 9), planes=(40, 30, 45), m=8, seed=5)
+    s = Step(sc, *oblique(66003), n_max=256)
+    ref = s.buffers()
+    s.run(*ref, s.need)
+    for nbytes in (s.need + s.records - 257, s.need + s.records + 4096):
+        got = s.buffers()
+        s.run(*got, nbytes)
+        assert_same(ref, got)
+    got = s.buffers()
+    om.render_fwd_bwd_l2(s.scene, s.o, s.d, s.target, got[0], got[1], loss=got[2], **s.kw)
+    assert_same(ref, got)
+    sizes = [om.fwd_bwd_l2_records_size(s.scene, n, 256) for n in (0, 1, 65536, 65537)]
+    assert sizes[:3] == [0, 0, 0] and sizes[3] > 0
+    with pytest.raises(om.OmerfError):
+        om.fwd_bwd_l2_records_size(s.scene, -1, 256)
+    with pytest.raises(om.OmerfError):
+        om.fwd_bwd_l2_records_size(s.scene, 65537, 0)
+
+
+def test_capture():
+    log("test_capture")
+    sc = micro_scene(grid=(20, 18, 9), planes=(40, 30, 45), m=8, seed=5)
+    s = Step(sc, *oblique(66003), n_max=256)
+    want = s.buffers()
+    s.run(*want, s.need + s.records)
+    got = s.buffers()
+    ws = torch.empty(s.need + s.records, dtype=torch.uint8, device=DEV)
+    step = lambda: om.render_fwd_bwd_l2(s.scene, s.o, s.d, s.target, got[0], got[1], loss=got[2],  # noqa: E731
+                                        workspace=ws, **s.kw)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.current_stream().wait_stream(side)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        step()
+    for _ in range(3):
+        for v in got[1].values():
+            v.zero_()
+        ws.fill_(255)
+        g.replay()
+        torch.cuda.synchronize()
+        assert_same(want, got)
+        s.run(*s.buffers(), s.need + s.records)
