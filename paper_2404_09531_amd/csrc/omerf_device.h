@@ -590,11 +590,21 @@ __device__ __forceinline__ void gather_u8(const SceneDev& sc, const Corners& c, 
 }
 
 // Block index -> virtual block index such that the blocks the hardware
-// places on one XCD (round-robin over 8 XCDs) cover one contiguous range of
-// rays, keeping neighbouring rays in the same L2.
+// places on one XCD (round-robin over 8 XCDs) cover runs of kXcdRun virtual
+// blocks (512 rays of the march), keeping neighbouring rays in the same L2.
+// The runs take turns over the XCDs: with one contiguous eighth of the rays per
+// XCD, the XCD with the far part of an image finished last while others idled.
+// 1920x1080 float32 10.54 ms with eighths, 9.19 / 9.15 / 9.16 / 9.19 with runs
+// of 4 / 16 / 64 / 256 blocks; 333x251 bf16 485 us, 409 / 412 / 401 / 446.
+constexpr uint32_t kXcdRun = 32;
+
 __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nb) {
+    const uint32_t full = nb / (8 * kXcdRun) * (8 * kXcdRun);  // in whole turns; the rest in eighths
+    if (b < full) return b / (8 * kXcdRun) * (8 * kXcdRun) + b % 8 * kXcdRun + b % (8 * kXcdRun) / 8;
+    b -= full;
+    nb -= full;
     const uint32_t per = nb / 8, rem = nb % 8, x = b % 8, i = b / 8;
-    return x < rem ? x * (per + 1) + i : rem * (per + 1) + (x - rem) * per + i;
+    return full + (x < rem ? x * (per + 1) + i : rem * (per + 1) + (x - rem) * per + i);
 }
 
 // ---------------------------------------------------------------------------
