@@ -136,26 +136,132 @@ __device__ __forceinline__ void store_group_total(float x, int gl, float* dst) {
 // segment instead of spilled scalar registers, and one offset per channel
 // instead of four, took a 1920x1080 frame with sparse blocks and early
 // termination from 3.78 to 2.97 ms.  bfloat16 is bound by L1 line lookups
-// (1.08 per clock, 36 per load instruction): 34.1 ms for 3840x2160 either way.
+// (1.19 per clock, 36 per load instruction).
 // ---------------------------------------------------------------------------
+// A sample as the lane that owns it holds it for the other lanes of its quad.
+struct QuadSample {
+    uint32_t g, xy, xz, yz;              // row keys (RowAddr)
+    float fx, fy, fz, ux, uy, uz;        // grid and plane fractions
+};
+
+template <bool kNarrow, int kBytes>
+__device__ __forceinline__ QuadSample quad_sample(const Corners& c) {
+    using A = RowAddr<kNarrow, kBytes>;
+    return QuadSample{A::key(c.g), A::key(c.xy), A::key(c.xz), A::key(c.yz), c.fx, c.fy, c.fz, c.ux, c.uy, c.uz};
+}
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// kLanes: the lanes that gather together, which all have to be there; kStage:
+// bytes of LDS per wave.
 struct GatherU8 {
+    static constexpr int kLanes = 1, kStage = 0;
     template <bool kNarrow>
-    static __device__ __forceinline__ void run(const SceneDev& sc, const Corners& c, float* t) {
+    static __device__ __forceinline__ void run(const SceneDev& sc, const Corners& c, int, char*, float* t) {
         gather_u8<kNarrow>(sc, c, t);
     }
 };
 struct GatherBF16 {
+    static constexpr int kLanes = 1, kStage = 0;
     template <bool kNarrow>
-    static __device__ __forceinline__ void run(const SceneDev& sc, const Corners& c, float* t) {
+    static __device__ __forceinline__ void run(const SceneDev& sc, const Corners& c, int, char*, float* t) {
         gather_features_split<BF16Store, kNarrow>(sc, c, t);
+    }
+};
+
+// Rows through LDS: lanes 2i and 2i + 1 of a quad load the two texels of a
+// corner pair straight into LDS, first for samples 0 and 1 of the quad, then
+// for 2 and 3, so that a load has 32 contiguous bytes of two samples per quad
+// and not 16 of four; each lane then reads its own sample's two texels there.
+// Where consecutive samples lie in different texel rows the L1 looks up 25
+// lines per load instead of 36, and three rows are in flight without holding
+// registers (two: 25.8 ms for 3840x2160, four at fewer waves: 28.3).  The sums
+// are those of GatherBF16 in the same order.
+//
+// One lane per sample and this, by the texels per step and axis: 1 (planes of
+// 4096 x 4096 x 512) 31.3 and 25.6 ms for 3840x2160, 8.07 and 6.69 for
+// 1920x1080, 0.617 and 0.625 for 333x251, sparse blocks 7.71 and 6.83; 0.5
+// 1.69 and 1.49 (960x540), 0.291 and 0.266 (333x251); 0.19 1.53 and 1.47, 0.283
+// and 0.277; 0.12 1.46 and 1.45, 0.271 and 0.273; 0.06 1.41 and 1.44, 0.253 and
+// 0.263.  A training step's rays share few lines, and its forward gains nothing
+// (2^20 rays 21.4 and 21.5 ms).
+struct GatherBF16Lds {
+    static constexpr int kLanes = 4;
+    static constexpr int kAhead = 3;                // rows in flight
+    static constexpr int kHalf = 64 * 16 + 16;      // a load, and 16 bytes so that the quad's reads miss each other's banks
+    static constexpr int kRow = kHalf + 64 * 16;
+    static constexpr int kStage = kAhead * kRow;    // with the queues 26,816 bytes per block: six per CU
+
+    template <int kPerm, bool kNarrow>
+    static __device__ __forceinline__ void load(const void* base, uint32_t stride, uint32_t key, uint32_t lane_off,
+                                                char* dst) {
+        using A = RowAddr<kNarrow, BF16Store::kBytes>;
+        const uint32_t k = quad_perm<kPerm>(key);
+        const char* p = kNarrow ? A::at(base, stride, k + lane_off) : A::at(base, stride, k) + lane_off;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
+                                         (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    }
+
+    // The lane's two texels of a row once at most kNewer later loads are out.
+    template <int kNewer>
+    static __device__ __forceinline__ void read(uint32_t at, u32x4& x0, u32x4& x1) {
+        asm volatile(
+            "s_waitcnt vmcnt(%3)\n\tds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)"
+            : "=&v"(x0), "=&v"(x1)
+            : "v"(at), "n"(kNewer)
+            : "memory");
+    }
+
+    template <bool kNarrow>
+    static __device__ __forceinline__ void run(const SceneDev& sc, const Corners& c, int lane, char* stage, float* t) {
+        const QuadSample o = quad_sample<kNarrow, BF16Store::kBytes>(c);
+        const uint32_t lane_off = lane & 1 ? 16u : 0u;
+        const uint32_t sy = sc.gsy, sz = sc.gsz, nx = (uint32_t)sc.Nx, ny = (uint32_t)sc.Ny;
+        const void* base[10] = {sc.grid, sc.grid, sc.grid, sc.grid, sc.pxy, sc.pxy, sc.pxz, sc.pxz, sc.pyz, sc.pyz};
+        const uint32_t stride[10] = {0u, sy, sz, sz + sy, 0u, nx, 0u, nx, 0u, ny};
+        const uint32_t key[10] = {o.g, o.g, o.g, o.g, o.xy, o.xy, o.xz, o.xz, o.yz, o.yz};
+        auto issue = [&](int j) {
+            char* dst = stage + j % kAhead * kRow;
+            load<0x50, kNarrow>(base[j], stride[j], key[j], lane_off, dst);          // samples 0, 0, 1, 1
+            load<0xFA, kNarrow>(base[j], stride[j], key[j], lane_off, dst + kHalf);  // 2, 2, 3, 3
+        };
+        const uint32_t own = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)stage +
+                             (uint32_t)((lane & 2 ? kHalf : 0) + ((lane & ~3) + (lane & 1) * 2) * 16);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = 0.0f;
+        auto row = [&](auto jc, float w0, float w1) {
+            constexpr int j = decltype(jc)::value, newer = 2 * (j + kAhead <= 10 ? kAhead - 1 : 9 - j);
+            u32x4 x0, x1;
+            read<newer>(own + j % kAhead * kRow, x0, x1);
+            if (j + kAhead < 10) issue(j + kAhead);
+            BF16Store::acc(make_uint4(x0.x, x0.y, x0.z, x0.w), w0, t);
+            BF16Store::acc(make_uint4(x1.x, x1.y, x1.z, x1.w), w1, t);
+        };
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) issue(j);
+        const float x0 = 1.0f - c.fx, x1 = c.fx, y0 = 1.0f - c.fy, y1 = c.fy, z0 = 1.0f - c.fz, z1 = c.fz;
+        const float a0 = 1.0f - c.ux, a1 = c.ux, b0 = 1.0f - c.uy, b1 = c.uy, e0 = 1.0f - c.uz, e1 = c.uz;
+        row(std::integral_constant<int, 0>{}, x0 * (y0 * z0), x1 * (y0 * z0));
+        row(std::integral_constant<int, 1>{}, x0 * (y1 * z0), x1 * (y1 * z0));
+        row(std::integral_constant<int, 2>{}, x0 * (y0 * z1), x1 * (y0 * z1));
+        row(std::integral_constant<int, 3>{}, x0 * (y1 * z1), x1 * (y1 * z1));
+        row(std::integral_constant<int, 4>{}, a0 * b0, a1 * b0);
+        row(std::integral_constant<int, 5>{}, a0 * b1, a1 * b1);
+        row(std::integral_constant<int, 6>{}, a0 * e0, a1 * e0);
+        row(std::integral_constant<int, 7>{}, a0 * e1, a1 * e1);
+        row(std::integral_constant<int, 8>{}, b0 * e0, b1 * e0);
+        row(std::integral_constant<int, 9>{}, b0 * e1, b1 * e1);
     }
 };
 
 // Waves per SIMD the one-lane-per-sample forwards are compiled for: without
 // the soft occupancy and with 32-bit addresses they fit 6 (<= 80 VGPRs)
-// without spilling; the other forms keep the compiler's choice.
+// without spilling, with records or two lanes per row 5; the other forms keep
+// the compiler's choice.
 template <class Gather, int kSave, bool kSoft, bool kNarrow>
-constexpr int lane_min_waves() { return !kSoft && kNarrow ? (kSave == kSaveRecords ? 5 : 6) : 1; }
+constexpr int lane_min_waves() {
+    return !kSoft && kNarrow ? (kSave == kSaveRecords ? 5 : 6) : 1;
+}
 
 template <class Gather, int kSave, bool kSoft, bool kSparse, bool kNarrow>
 __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarrow>())) void k_march_fwd_lane(
@@ -163,6 +269,8 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarr
     float* __restrict__ F, float* __restrict__ T, int32_t* __restrict__ n_placed, int32_t* __restrict__ n_eval,
     float* __restrict__ BW, BatchRecords br) {
     __shared__ int qs[kGroupsPerBlock][kQueue];
+    __shared__ __attribute__((aligned(16))) char stages[Gather::kStage ? kBlock / 64 * Gather::kStage : 16];
+    char* stage = stages + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) * Gather::kStage;
     const int lane = threadIdx.x & 63;
     const int gl = lane & (kGroup - 1);
     const int gid = threadIdx.x / kGroup;
@@ -183,10 +291,10 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarr
 #pragma unroll
         for (int c = 0; c < 8; ++c) t[c] = 0.0f;
         float msoft = 0.0f;
-        if (act) {
+        if ((gl & -Gather::kLanes) < nb) {
             const float3 p = lattice_point(kq, o, d, rp.delta);
             const SceneDev& sa = scene_argument();
-            Gather::template run<kNarrow>(sa, corners_of<kSparse, kNarrow>(sa, p), t);
+            Gather::template run<kNarrow>(sa, corners_of<kSparse, kNarrow>(sa, p), lane, stage, t);
             if (kSoft) msoft = occ_value(sc, p, rp.occ_inv_eps).m;
         }
         float a = 0.0f;
@@ -269,11 +377,6 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarr
 // 1920x1080 frame of the full-size scene 13.98 ms; now some 600 and 10.52 ms,
 // with the L1 looking up 0.9 lines per clock.
 // ---------------------------------------------------------------------------
-struct QuadSample {
-    uint32_t g, xy, xz, yz;              // row keys (RowAddr)
-    float fx, fy, fz, ux, uy, uz;        // grid and plane fractions
-};
-
 // Sample 4j + s of the quad, j = kJ: the lane's half of the channels, summed
 // over the rows at its x-offset.  lane_off: the lane's 16 bytes within a
 // corner pair; hs, h0: its x weight is h0 + hs * fraction.
@@ -341,12 +444,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
     const int slot = kSave == kSaveRecords ? br.slot_of_ray[ray] : -1;
     const int alloc = kSave == kSaveRecords ? (n_placed[ray] + kGroup - 1) / kGroup : 0;
     const int placed = march_candidates(sc, rp, o, d, qs[gid], gl, pos, lane, [&](int kq, int nb) {
-        QuadSample own;
-        {
-            const Corners c = corners_of<kSparse, kNarrow>(scene_argument(), lattice_point(kq, o, d, rp.delta));
-            using A = RowAddr<kNarrow, 32>;
-            own = QuadSample{A::key(c.g), A::key(c.xy), A::key(c.xz), A::key(c.yz), c.fx, c.fy, c.fz, c.ux, c.uy, c.uz};
-        }
+        const QuadSample own = quad_sample<kNarrow, 32>(
+            corners_of<kSparse, kNarrow>(scene_argument(), lattice_point(kq, o, d, rp.delta)));
         const SceneDev& sa = scene_argument();
         float v0[4], v1[4], t0 = 0.0f;
         auto quarter = [&](auto jc) {
@@ -487,6 +586,12 @@ bool narrow_scene(const SceneDev& sc, int dtype) {
            (uint64_t)sc.Nx * (uint64_t)sc.Nz * bytes <= most && (uint64_t)sc.Ny * (uint64_t)sc.Nz * bytes <= most;
 }
 
+// Whether a step crosses 0.15 of a plane texel or more on every axis: where it
+// crosses less, the samples of a quad share their rows anyway (GatherBF16Lds).
+static bool fine_planes(const SceneDev& sc, float delta) {
+    return fminf(sc.px.s, fminf(sc.py.s, sc.pz.s)) * delta >= 0.15f;
+}
+
 template <bool kSoft, bool kSparse, bool kNarrow>
 static void launch_fwd_form(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
                             int64_t n, float* F, float* T, int32_t* n_placed, int32_t* n_eval, float* batch_wv,
@@ -502,9 +607,14 @@ static void launch_fwd_form(const SceneDev& sc, int dtype, const RayParams& rp, 
     static constexpr Kernel bf16[3] = {k_march_fwd_lane<GatherBF16, kSaveNone, kSoft, kSparse, kNarrow>,
                                        k_march_fwd_lane<GatherBF16, kSums, kSoft, kSparse, kNarrow>,
                                        k_march_fwd_lane<GatherBF16, kRecs, kSoft, kSparse, kNarrow>};
+    // Rows through LDS: plain renders of scenes with 32-bit addresses.
+    constexpr bool kLds = kNarrow && !kSoft;
+    static constexpr Kernel bf16_lds =
+        k_march_fwd_lane<std::conditional_t<kLds, GatherBF16Lds, GatherBF16>, kSaveNone, kSoft, kSparse, kNarrow>;
     const int save = br ? kSaveRecords : batch_wv ? kSaveSums : kSaveNone;
+    const bool lds = kLds && save == kSaveNone && fine_planes(sc, rp.delta);
     const Kernel k = dtype == OM_U8 ? k_march_fwd_lane<GatherU8, kSaveNone, kSoft, kSparse, kNarrow>
-                                    : dtype == OM_BF16 ? bf16[save] : f32[save];
+                                    : dtype == OM_BF16 ? (lds ? bf16_lds : bf16[save]) : f32[save];
     hipLaunchKernelGGL(k, dim3(blocks_for(n)), dim3(kBlock), 0, s, sc, rp, o, d, n, F, T, n_placed, n_eval, batch_wv,
                        br ? *br : BatchRecords{});
 }

@@ -472,6 +472,12 @@ __device__ __forceinline__ uint32_t quad_bcast(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x55 * kLane, 0xf, 0xf, false);
 }
 
+// The quad's value under a DPP quad permutation (2 bits per lane).
+template <int kPerm>
+__device__ __forceinline__ uint32_t quad_perm(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kPerm, 0xf, 0xf, false);
+}
+
 // Value of lane kLane of the 16-lane row (DPP row_newbcast).
 template <int kLane>
 __device__ __forceinline__ float row_bcast(float x) {
