@@ -394,7 +394,8 @@ int64_t om_render_fwd_bwd_l2_workspace_size(int64_t n, const om_params* p);
 
 /*
  * Workspace beyond om_render_fwd_bwd_l2_workspace_size(n, p) with which
- * om_render_fwd_bwd_l2 keeps a record per 16-sample batch between the forward
+ * om_render_fwd_bwd_l2 takes the rays in a locality order of its own (results
+ * stay in the caller's), keeps a record per 16-sample batch between the forward
  * and the backward, instead of replaying the samples, and sums the XZ and YZ
  * gradients by tiles instead of one float atomic per segment: bytes to add (p:
  * only n_max is read), 0 where that would not pay for this scene and batch, -1

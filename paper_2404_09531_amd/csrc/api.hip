@@ -512,7 +512,7 @@ int check_fwd_bwd_l2(const om_scene* scene, const float* o, const float* d, int6
 // the backward's workspace (om_render_backward_workspace_size: per-ray dL/dF
 // and background term, ray order, scheduling words) | per-batch sums of
 // w v]: forward with per-batch sums, loss gradient, MLP backward, march
-// backward.  With `records` the rays are counted and ordered first, so that
+// backward.  With `records` the rays are ordered and counted first, so that
 // the forward can leave its batch records and the backward need not replay.
 int fwd_bwd_l2_launch(const om_scene* scene, const float* o, const float* d, int64_t n, const om_params* p,
                       const RayParams& rp, const float* target, const om_fwd_out* out, void* workspace, void* records,
@@ -529,7 +529,9 @@ int fwd_bwd_l2_launch(const om_scene* scene, const float* o, const float* d, int
     if (records) {
         record_workspace(scene->dev, n, rp.n_max, records, &br, &tl);
         brp = &br;
-        e = launch_count(scene->dev, rp, o, d, n, out->n_placed, s);
+        e = launch_order_rays(scene->desc.box_lo, scene->desc.box_hi, o, d, n, br.ray_at, nullptr, nullptr, br.hist,
+                              br.keys, s);
+        if (e == hipSuccess) e = launch_count(scene->dev, rp, o, d, n, br.ray_at, out->n_placed, s);
         if (e == hipSuccess) e = launch_bwd_order(out->n_placed, n, rp.n_max, w.order, w.sched, brp, s);
         if (e != hipSuccess) return hip_status(e, who);
     }

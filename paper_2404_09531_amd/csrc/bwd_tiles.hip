@@ -318,20 +318,25 @@ int64_t record_workspace(const SceneDev& sc, int64_t n, int n_max, void* base, B
     const int64_t nu_x = (sc.Nx - 2) / kTileU + 1, nu_y = (sc.Ny - 2) / kTileU + 1, nv = (sc.Nz - 2) / kTileV + 1;
     const int64_t bins = (nu_x + nu_y) * nv;
     if (batches <= kRecordBatches || bins > kTileMaxBins) return 0;
-    const int64_t parts[6] = {cap * kRecFloats * (int64_t)sizeof(float),
+    const int64_t parts[9] = {cap * kRecFloats * (int64_t)sizeof(float),
                               n * (int64_t)sizeof(int32_t),
                               cap * kKeysPerBatch * (int64_t)sizeof(uint16_t),
                               cap * kKeysPerBatch * (int64_t)sizeof(int32_t),
                               2 * bins * (int64_t)sizeof(int),
-                              (int64_t)sizeof(int)};
+                              (int64_t)sizeof(int),
+                              n * (int64_t)sizeof(int32_t),
+                              order_hist_bytes(),
+                              n * (int64_t)sizeof(uint16_t)};
     char* p = static_cast<char*>(base);
-    int64_t at[6], total = 0;
-    for (int i = 0; i < 6; ++i) {
+    int64_t at[9], total = 0;
+    for (int i = 0; i < 9; ++i) {
         at[i] = total;
         total += align256(parts[i]);
     }
     if (p) {
-        *br = BatchRecords{reinterpret_cast<float*>(p + at[0]), reinterpret_cast<int32_t*>(p + at[1]), (int)cap};
+        *br = BatchRecords{reinterpret_cast<float*>(p + at[0]), reinterpret_cast<int32_t*>(p + at[1]),
+                           reinterpret_cast<int32_t*>(p + at[6]), reinterpret_cast<int*>(p + at[7]),
+                           reinterpret_cast<uint16_t*>(p + at[8]), (int)cap};
         *tl = TileLists{reinterpret_cast<uint16_t*>(p + at[2]), reinterpret_cast<int32_t*>(p + at[3]),
                         reinterpret_cast<int*>(p + at[4]),   reinterpret_cast<int*>(p + at[5]),
                         (int)bins,                           (int)(nu_x * nv),

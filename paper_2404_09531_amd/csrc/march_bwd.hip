@@ -526,8 +526,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
 // Bound by the scatter's float atomics: 82 million 64-byte requests of 2^18
 // rays in float32 in 4.5 ms, near the 20.6 G/s that they reach beyond L2
 //.  The step took 12.3 ms with
-// the samples replayed and four sources scattered; the forward with records
-// (3.3), the counts ahead of it (0.25), this and the tiles' sums take 11.1.
+// the samples replayed and four sources scattered; the rays' order (0.09), their
+// counts (0.23), the forward with records (2.6), this and the tiles' sums (2.9)
+// take 10.4.
 // ---------------------------------------------------------------------------
 struct RecordLoad {
     float a, v[7], px, py, pz, carry;

@@ -42,20 +42,25 @@ __global__ __launch_bounds__(kBlock) void k_place(SceneDev sc, RayParams rp, con
 // The counts alone, ahead of a training step that gives every batch a record.
 __global__ __launch_bounds__(kBlock) void k_count(SceneDev sc, RayParams rp, const float* __restrict__ o_,
                                                   const float* __restrict__ d_, int64_t n,
-                                                  int32_t* __restrict__ n_placed) {
+                                                  const int32_t* __restrict__ ray_at, int32_t* __restrict__ n_placed) {
     __shared__ int qs[kGroupsPerBlock][kQueue];
     const int lane = threadIdx.x & 63;
     const int gl = lane & (kGroup - 1);
     const int gid = threadIdx.x / kGroup;
-    const int64_t ray = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGroupsPerBlock + gid;
-    if (ray >= n) return;
+    const int64_t at = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGroupsPerBlock + gid;
+    if (at >= n) return;
+    const int64_t ray = ray_at[at];
     const int cnt = march_candidates(sc, rp, load3(o_, ray), load3(d_, ray), qs[gid], gl, gl, lane,
                                      [](int, int) { return false; });
     if (gl == 0) n_placed[ray] = cnt;
 }
 
 // What a forward leaves for the backward: nothing, the per-batch sums of w v,
-// or a record per batch (the sums for rays without records).
+// or a record per batch (the sums for rays without records).  With records,
+// batches of many rays, the rays are taken in the locality order: the forward
+// of 2^18 rays of 16 cameras in float32 2.81 ms as they come and 1.96 so, of
+// 2^20 of 64 in bfloat16 5.27 and 3.63, for 0.05 to 0.15 ms that ordering them
+// costs.
 enum { kSaveNone, kSaveSums, kSaveRecords };
 
 // Marks the ray's records from `batch` on, which it did not reach (early
@@ -274,8 +279,9 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarr
     const int lane = threadIdx.x & 63;
     const int gl = lane & (kGroup - 1);
     const int gid = threadIdx.x / kGroup;
-    const int64_t ray = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGroupsPerBlock + gid;
-    if (ray >= n) return;
+    const int64_t at = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGroupsPerBlock + gid;
+    if (at >= n) return;
+    const int64_t ray = kSave == kSaveRecords ? (int64_t)br.ray_at[at] : at;
     const float3 o = load3(o_, ray), d = load3(d_, ray);
     float acc[7];
 #pragma unroll
@@ -434,8 +440,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
     const int pos = 4 * q + (gl >> 2);  // the lane's own sample of a batch
     const uint32_t lane_off = (uint32_t)(h * 32 + (gl & 2) * 8);
     const float hs = h ? 1.0f : -1.0f, h0 = h ? 0.0f : 1.0f;
-    const int64_t ray = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGroupsPerBlock + gid;
-    if (ray >= n) return;
+    const int64_t at = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGroupsPerBlock + gid;
+    if (at >= n) return;
+    const int64_t ray = kSave == kSaveRecords ? (int64_t)br.ray_at[at] : at;
     const float3 o = load3(o_, ray), d = load3(d_, ray);
     float acc0 = 0.0f, acc1 = 0.0f;  // channels 2q and 2q + 1 (0 is the density)
     float carry = 0.0f;
@@ -551,8 +558,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
 static inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kGroupsPerBlock - 1) / kGroupsPerBlock); }
 
 hipError_t launch_count(const SceneDev& sc, const RayParams& rp, const float* o, const float* d, int64_t n,
-                        int32_t* n_placed, hipStream_t s) {
-    hipLaunchKernelGGL(k_count, dim3(blocks_for(n)), dim3(kBlock), 0, s, sc, rp, o, d, n, n_placed);
+                        const int32_t* ray_at, int32_t* n_placed, hipStream_t s) {
+    hipLaunchKernelGGL(k_count, dim3(blocks_for(n)), dim3(kBlock), 0, s, sc, rp, o, d, n, ray_at, n_placed);
     return hipGetLastError();
 }
 

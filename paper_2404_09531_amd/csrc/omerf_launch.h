@@ -27,13 +27,17 @@ constexpr int kRecPoint = 8 * kGroup, kRecCarry = 11 * kGroup, kRecFloats = 12 *
 // A fused step keeps records where n rays of at most n_max samples may have
 // more than kRecordBatches batches and the placement counts find at least
 // kRecordMin.  Steps with and without them: 423,000 batches (of 524,288)
-// 1.81 and 1.77 ms, 637,000 (of 2^20) 3.32 and 3.43, 2.54 million 11.2 and
-// 12.3, 5.1 million in bfloat16 20.7 and 23.0; below, the planes' tiles are
-// too thinly covered to pay for their sums (212,000: 1.15 and 1.06).
+// 1.83 and 1.78 ms, 637,000 (of 2^20) 3.29 and 3.43, 1.27 million 5.7 and 6.4,
+// 2.54 million 10.4 and 12.3, 5.1 million in bfloat16 18.9 and 23.0; below, the
+// planes' tiles are too thinly covered to pay for their sums (212,000: 1.22 and
+// 1.07).
 constexpr int64_t kRecordBatches = 1 << 20, kRecordMin = 1 << 19;
 struct BatchRecords {
     float* rec;
     int32_t* slot_of_ray;  // [n] first record of each ray, -1: none
+    int32_t* ray_at;       // [n] locality order of the rays, for the passes over the scene
+    int* hist;             // its histogram (order_hist_bytes)
+    uint16_t* keys;        // [n] and keys
     int cap;               // records
 };
 // Where sample i of a batch stands in a channel row as the forward writes it:
@@ -45,9 +49,9 @@ __host__ __device__ constexpr int record_place(int i) { return 4 * (i & 3) + (i 
 hipError_t launch_march_fwd(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
                             int64_t n, float* F, float* T, int32_t* n_placed, int32_t* n_eval, float* batch_wv,
                             const BatchRecords* br, hipStream_t s);
-// Samples placed per ray.
+// Samples placed per ray; ray_at: a permutation of the rays to take them in.
 hipError_t launch_count(const SceneDev& sc, const RayParams& rp, const float* o, const float* d, int64_t n,
-                        int32_t* n_placed, hipStream_t s);
+                        const int32_t* ray_at, int32_t* n_placed, hipStream_t s);
 // Scheduling words (int32) of the march backward in its workspace: the
 // ray-order histogram, its cursors and the hand-out counters, and the slots of
 // the rays' records.

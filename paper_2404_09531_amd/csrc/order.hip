@@ -17,12 +17,14 @@
 //                  scatter); each run of equal keys among consecutive rays
 //                  of a wave adds its length once.
 // k_okey_scan    : exclusive prefix sum of the histogram, in place (one
-//                  block; 64 bins per thread).
+//                  block; a wave takes 4,096 bins, 256 per load.  With 64
+//                  consecutive bins per thread, whose loads share no lines,
+//                  it took 27 us).
 // k_okey_scatter : reads the stored keys, so its runs are those the
 //                  histogram counted and every slot lies in [0, n); each
 //                  run reserves its slots in its bin with one atomic
 //                  and its rays take consecutive slots in input order;
-//                  writes order[slot] = ray and the ray's origin and
+//                  writes order[slot] = ray and (kRows) the ray's origin and
 //                  direction at that slot.  Runs of one bin land in the
 //                  order their atomics are served.
 // k_rows_gather / k_rows_scatter : dst[i] = src[idx[i]] and
@@ -39,7 +41,8 @@ constexpr int kOrderBlock = 256;
 constexpr int kAxisBits = 8;
 constexpr int kKeyBins = 1 << (2 * kAxisBits);
 constexpr int kScanThreads = 1024;
-constexpr int kBinsPerThread = kKeyBins / kScanThreads;
+constexpr int kScanWaves = kScanThreads / 64;
+constexpr int kScanLoads = kKeyBins / (kScanThreads * 4);  // of four bins, per thread
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
 // The key's lattice: footprint origin, cells per unit length, and the
@@ -107,27 +110,38 @@ __global__ void __launch_bounds__(kOrderBlock) k_okey_hist(const float* __restri
 }
 
 __global__ void __launch_bounds__(kScanThreads) k_okey_scan(int* hist) {
-    __shared__ int part[kScanThreads];
-    const int t = threadIdx.x;
-    int* bins = hist + t * kBinsPerThread;
-    int sum = 0;
-    for (int j = 0; j < kBinsPerThread; ++j) sum += bins[j];
-    part[t] = sum;
+    __shared__ int part[kScanWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int4* bins = reinterpret_cast<int4*>(hist) + wave * kScanLoads * 64 + lane;
+    int4 c[kScanLoads];
+#pragma unroll
+    for (int j = 0; j < kScanLoads; ++j) c[j] = bins[j * 64];
+    int upto[kScanLoads];  // through the lane's four bins, of load j's 256
+#pragma unroll
+    for (int j = 0; j < kScanLoads; ++j) upto[j] = c[j].x + c[j].y + c[j].z + c[j].w;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+        for (int j = 0; j < kScanLoads; ++j) {
+            const int v = __shfl_up(upto[j], off);
+            if (lane >= off) upto[j] += v;
+        }
+    int total = 0;
+#pragma unroll
+    for (int j = 0; j < kScanLoads; ++j) total += __shfl(upto[j], 63);
+    if (lane == 0) part[wave] = total;
     __syncthreads();
-    for (int off = 1; off < kScanThreads; off <<= 1) {
-        const int v = t >= off ? part[t - off] : 0;
-        __syncthreads();
-        part[t] += v;
-        __syncthreads();
-    }
-    int run = part[t] - sum;
-    for (int j = 0; j < kBinsPerThread; ++j) {
-        const int c = bins[j];
-        bins[j] = run;
-        run += c;
+    int run = 0;
+    for (int w = 0; w < wave; ++w) run += part[w];
+#pragma unroll
+    for (int j = 0; j < kScanLoads; ++j) {
+        const int z = run + upto[j] - c[j].w, y = z - c[j].z, x = y - c[j].y;
+        bins[j * 64] = make_int4(x - c[j].x, x, y, z);
+        run += __shfl(upto[j], 63);
     }
 }
 
+template <bool kRows>
 __global__ void __launch_bounds__(kOrderBlock) k_okey_scatter(const float* __restrict__ o, const float* __restrict__ d,
                                                                int64_t n, const uint16_t* __restrict__ keys,
                                                                int* __restrict__ cursor,
@@ -144,6 +158,7 @@ __global__ void __launch_bounds__(kOrderBlock) k_okey_scatter(const float* __res
     const int64_t slot = (int64_t)base + (lane - head);
     if (key == kNoKey || slot >= n) return;
     order[slot] = (int32_t)i;
+    if (!kRows) return;
     for (int c = 0; c < 3; ++c) {
         o_out[3 * slot + c] = o[3 * i + c];
         d_out[3 * slot + c] = d[3 * i + c];
@@ -186,7 +201,7 @@ hipError_t launch_order_rays(const float* box_lo, const float* box_hi, const flo
     hipLaunchKernelGGL(k_okey_clear, dim3(blocks_for(kKeyBins)), dim3(kOrderBlock), 0, s, hist);
     hipLaunchKernelGGL(k_okey_hist, dim3(blocks_for(n)), dim3(kOrderBlock), 0, s, o, d, n, kf, keys, hist);
     hipLaunchKernelGGL(k_okey_scan, dim3(1), dim3(kScanThreads), 0, s, hist);
-    hipLaunchKernelGGL(k_okey_scatter, dim3(blocks_for(n)), dim3(kOrderBlock), 0, s, o, d, n, keys, hist, order, o_out,
+    hipLaunchKernelGGL(o_out ? k_okey_scatter<true> : k_okey_scatter<false>, dim3(blocks_for(n)), dim3(kOrderBlock), 0, s, o, d, n, keys, hist, order, o_out,
                        d_out);
     return hipGetLastError();
 }
