@@ -263,35 +263,48 @@ __device__ __forceinline__ void wave_mlp_bwd(const float* W, const float* xs, in
     acc.b3 += d3;
 }
 
-// Adds a wave's accumulators to the block's LDS copy of the gradient
-// (SIZE floats, MlpLayout order).
+// Sum over the wave's four groups of their lanes at the same place.
+__device__ __forceinline__ float across_groups(float x) {
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
+// Stores a wave's accumulators as its own copy of the gradient in LDS (SIZE
+// floats, MlpLayout order, every one written): LDS float atomics are performed
+// one lane at a time (195 cycles per wave instruction), so the waves of a block
+// share no copy.  k_mlp_bwd with one copy per block took 18.5 / 36 / 71 us for
+// 2^12 / 2^14 / 2^18 rays, with one per wave 8.2 / 13.3 / 52 us.
 template <int NIN>
-__device__ __forceinline__ void mlp_grad_to_lds(const MlpGradAcc<NIN>& acc, int lane, float* sW) {
+__device__ __forceinline__ void mlp_grad_store(const MlpGradAcc<NIN>& acc, int lane, float* sW) {
     using L = MlpLayout<NIN>;
     const int col = lane & 15, row0 = (lane >> 4) * 4;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int row = row0 + r;
-        atomicAdd(&sW[L::W2 + row * 16 + col], acc.w2[r]);
-        if (row < 3) atomicAdd(&sW[L::W3 + row * 16 + col], acc.w3[r]);
+        sW[L::W2 + row * 16 + col] = acc.w2[r];
+        if (row < 3) sW[L::W3 + row * 16 + col] = acc.w3[r];
 #pragma unroll
         for (int s = 0; s < MlpGradAcc<NIN>::kSlices; ++s) {
             const int c = 16 * s + col;
             if (c < NIN)
-                atomicAdd(&sW[L::W1 + row * NIN + c], acc.w1[s][r]);
+                sW[L::W1 + row * NIN + c] = acc.w1[s][r];
             else if (c == NIN)
-                atomicAdd(&sW[L::B1 + row], acc.w1[s][r]);
+                sW[L::B1 + row] = acc.w1[s][r];
         }
     }
-    atomicAdd(&sW[L::B2 + col], acc.b2);
-    if (col < 3) atomicAdd(&sW[L::B3 + col], acc.b3);
+    const float b2 = across_groups(acc.b2), b3 = across_groups(acc.b3);
+    if (lane < 16) sW[L::B2 + col] = b2;
+    if (lane < 3) sW[L::B3 + col] = b3;
 }
 
-// Adds the block's LDS gradient to gmlp (one float atomic per nonzero entry).
-template <int NIN>
-__device__ __forceinline__ void mlp_grad_flush(const float* sW, float* gmlp) {
+// Adds the copies of the block's waves to gmlp (one float atomic per nonzero
+// entry).
+template <int NIN, int kWaves>
+__device__ __forceinline__ void mlp_grad_flush(const float (*sW)[MlpLayout<NIN>::SIZE], float* gmlp) {
     for (int i = threadIdx.x; i < MlpLayout<NIN>::SIZE; i += blockDim.x) {
-        const float v = sW[i];
+        float v = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) v += sW[w][i];
         if (v != 0.0f) unsafeAtomicAdd(gmlp + i, v);
     }
 }
@@ -322,9 +335,7 @@ __global__ __launch_bounds__(mlp_bwd_block<NIN>()) void k_mlp_bwd(const float* _
                                                           int64_t n, int64_t quads_per_block, float* __restrict__ G8,
                                                           float* __restrict__ gmlp) {
     constexpr int kThreads = mlp_bwd_block<NIN>();
-    __shared__ float sW[MlpLayout<NIN>::SIZE];
-    for (int i = threadIdx.x; i < MlpLayout<NIN>::SIZE; i += kThreads) sW[i] = 0.0f;
-    __syncthreads();
+    __shared__ float sW[kThreads / 64][MlpLayout<NIN>::SIZE];
     const int lane = threadIdx.x & 63, gl = lane & (kGroup - 1), g = lane >> 4;
     const int64_t nq = (n + 3) / 4;
     const int64_t q0 = (int64_t)xcd_block(blockIdx.x, gridDim.x) * quads_per_block;
@@ -370,9 +381,9 @@ __global__ __launch_bounds__(mlp_bwd_block<NIN>()) void k_mlp_bwd(const float* _
             G8[ray * 8 + gl] = v;
         }
     }
-    mlp_grad_to_lds<NIN>(acc, lane, sW);
+    mlp_grad_store<NIN>(acc, lane, sW[threadIdx.x >> 6]);
     __syncthreads();
-    mlp_grad_flush<NIN>(sW, gmlp);
+    mlp_grad_flush<NIN, kThreads / 64>(sW, gmlp);
 }
 
 template <int NIN>
@@ -636,7 +647,7 @@ hipError_t launch_occ_loss(const float* occ, int64_t cells, float weight, float*
 // dL/dG), whose parameter gradients are reduced on MFMA per wave and in LDS
 // per block (MlpGradAcc); dL/dF is added to dF with float32 atomics (the P
 // pairs of a ray land in different groups).  The loss value is a float32
-// sum (per group, then one float32 atomic per group).
+// sum (per group and block, then one float32 atomic per block).
 // ---------------------------------------------------------------------------
 __global__ void k_zero_f32(float* p) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0.0f;
@@ -648,9 +659,8 @@ __global__ __launch_bounds__(kBlock) void k_smooth(const float* __restrict__ W, 
                                                    const float* __restrict__ perturb, int P, float weight,
                                                    float* __restrict__ loss, float* __restrict__ dF,
                                                    float* __restrict__ gmlp) {
-    __shared__ float sW[MlpLayout<NIN>::SIZE];
-    for (int i = threadIdx.x; i < MlpLayout<NIN>::SIZE; i += kBlock) sW[i] = 0.0f;
-    __syncthreads();
+    __shared__ float sW[kBlock / 64][MlpLayout<NIN>::SIZE];
+    __shared__ float wave_loss[kBlock / 64];
     const int lane = threadIdx.x & 63;
     const int gl = lane & (kGroup - 1);
     const int g = lane >> 4;
@@ -714,12 +724,17 @@ __global__ __launch_bounds__(kBlock) void k_smooth(const float* __restrict__ W, 
             unsafeAtomicAdd(dF + ray * 7 + gl, v);
         }
     }
-    if (loss && gl == 0 && acc != 0.0f) unsafeAtomicAdd(loss, acc);
-    if (gmlp) {
-        mlp_grad_to_lds<NIN>(macc, lane, sW);
-        __syncthreads();
-        mlp_grad_flush<NIN>(sW, gmlp);
+    acc = across_groups(acc);
+    if (lane == 0) wave_loss[threadIdx.x >> 6] = acc;
+    if (gmlp) mlp_grad_store<NIN>(macc, lane, sW[threadIdx.x >> 6]);
+    __syncthreads();
+    if (loss && threadIdx.x == 0) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) sum += wave_loss[w];
+        if (sum != 0.0f) unsafeAtomicAdd(loss, sum);
     }
+    if (gmlp) mlp_grad_flush<NIN, kBlock / 64>(sW, gmlp);
 }
 
 hipError_t launch_smooth(const float* W, int mlp_in, const float* F, const float* d, int64_t n, const float* perturb,
