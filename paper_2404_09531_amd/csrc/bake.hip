@@ -193,48 +193,81 @@ hipError_t launch_blocks_mark(const SceneDev& sc, int shift, int bnx, int bny, i
 }
 
 // Numbers the kept blocks 1.. in index order, in place (one workgroup; each
-// step scans a slice of consecutive entries, kNumberPer per thread).  The
+// step scans a slice of 16,384 consecutive entries, sixteen per thread as whole
+// 16-byte loads, the next slice's loaded meanwhile: 262,144 entries 42 us
+// instead of 242 with scalar loads that share no lines).  The
 // count goes out in entry 0, whose own id can only be 0 or 1: negated if it is
 // 1; k_blocks_first puts that id back.
 constexpr int kNumberThreads = 1024;
-constexpr int kNumberPer = 8;
+constexpr int kNumberLoads = 4;  // of four entries, per thread
+constexpr int kNumberSlice = kNumberThreads * kNumberLoads * 4;
 
+// Entries 4 at .. 4 at + 3 (zero past n); kWide: mark is 16-byte aligned.
+template <bool kWide>
+__device__ __forceinline__ int4 four_marks(const int32_t* mark, int64_t n, int64_t at) {
+    if (kWide && 4 * at + 4 <= n) return reinterpret_cast<const int4*>(mark)[at];
+    int4 m = make_int4(0, 0, 0, 0);
+    if (4 * at < n) m.x = mark[4 * at];
+    if (4 * at + 1 < n) m.y = mark[4 * at + 1];
+    if (4 * at + 2 < n) m.z = mark[4 * at + 2];
+    if (4 * at + 3 < n) m.w = mark[4 * at + 3];
+    return m;
+}
+
+template <bool kWide>
 __global__ __launch_bounds__(kNumberThreads) void k_blocks_number(int32_t* __restrict__ mark, int64_t n) {
-    __shared__ int wave_sum[kNumberThreads / 64];
+    __shared__ int wave_sum[2][kNumberThreads / 64];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    int base = 0;
-    bool first = false;
-    for (int64_t s = 0; s < n; s += kNumberThreads * kNumberPer) {
-        const int64_t i = s + (int64_t)t * kNumberPer;
-        int m[kNumberPer], c = 0;
+    int base = 0, turn = 0;
+    const bool first = t == 0 && mark[0] != 0;
+    int4 next[kNumberLoads];
 #pragma unroll
-        for (int k = 0; k < kNumberPer; ++k) {
-            m[k] = i + k < n ? mark[i + k] : 0;
-            c += m[k];
-        }
-        if (s == 0 && t == 0) first = m[0] != 0;
-        int sum = c;
+    for (int j = 0; j < kNumberLoads; ++j) next[j] = four_marks<kWide>(mark, n, (w * kNumberLoads + j) * 64 + lane);
+    for (int64_t s = 0; s < n; s += kNumberSlice, turn ^= 1) {
+        const int64_t at = s / 4 + w * kNumberLoads * 64 + lane;  // a wave: consecutive entries, 256 per load
+        int4 m[kNumberLoads];
+        int upto[kNumberLoads];
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int v = __shfl_up(sum, off);
-            if (lane >= off) sum += v;
+        for (int j = 0; j < kNumberLoads; ++j) {
+            m[j] = next[j];
+            next[j] = four_marks<kWide>(mark, n, at + kNumberSlice / 4 + j * 64);
+            upto[j] = m[j].x + m[j].y + m[j].z + m[j].w;
         }
-        if (lane == 63) wave_sum[w] = sum;
-        __syncthreads();
-        int before = 0, all = 0;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+            for (int j = 0; j < kNumberLoads; ++j) {
+                const int v = __shfl_up(upto[j], off);
+                if (lane >= off) upto[j] += v;
+            }
+        int total = 0;
+#pragma unroll
+        for (int j = 0; j < kNumberLoads; ++j) total += __shfl(upto[j], 63);
+        if (lane == 0) wave_sum[turn][w] = total;
+        __syncthreads();  // the other turn's sums are read before the next one
+        int id = base;
         for (int k = 0; k < kNumberThreads / 64; ++k) {
-            if (k < w) before += wave_sum[k];
-            all += wave_sum[k];
+            const int c = wave_sum[turn][k];
+            if (k < w) id += c;
+            base += c;
         }
-        int id = base + before + sum - c;
 #pragma unroll
-        for (int k = 0; k < kNumberPer; ++k) {
-            id += m[k];
-            if (i + k < n) mark[i + k] = m[k] ? id : 0;
+        for (int j = 0; j < kNumberLoads; ++j) {
+            const int d = id + upto[j], c = d - m[j].w, b = c - m[j].z, a = b - m[j].y;
+            const int4 out = make_int4(m[j].x ? a : 0, m[j].y ? b : 0, m[j].z ? c : 0, m[j].w ? d : 0);
+            const int64_t i = 4 * (at + j * 64);
+            if (kWide && i + 4 <= n) {
+                reinterpret_cast<int4*>(mark)[at + j * 64] = out;
+            } else {
+                if (i < n) mark[i] = out.x;
+                if (i + 1 < n) mark[i + 1] = out.y;
+                if (i + 2 < n) mark[i + 2] = out.z;
+                if (i + 3 < n) mark[i + 3] = out.w;
+            }
+            id += __shfl(upto[j], 63);
         }
-        base += all;
-        __syncthreads();
     }
+    __syncthreads();
     if (t == 0) mark[0] = first ? -base : base;
 }
 
@@ -243,7 +276,7 @@ __global__ void k_blocks_first(int32_t* mark, int id) {
 }
 
 hipError_t launch_blocks_number(int32_t* mark, int64_t n, hipStream_t s) {
-    hipLaunchKernelGGL(k_blocks_number, dim3(1), dim3(kNumberThreads), 0, s, mark, n);
+    hipLaunchKernelGGL((uintptr_t)mark & 15u ? k_blocks_number<false> : k_blocks_number<true>, dim3(1), dim3(kNumberThreads), 0, s, mark, n);
     return hipGetLastError();
 }
 
