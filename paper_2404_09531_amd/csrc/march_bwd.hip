@@ -190,7 +190,7 @@ __device__ __forceinline__ void scatter_batch_runs(const SceneDev& sc, float* gV
 
 // One replayed sample: optical depth, density, activated colours/features
 // and, for the soft occupancy, its value and derivatives.
-template <class S, bool kSoft, bool kNarrow>
+template <class S, bool kSoft, bool kNarrow, bool kFew>
 __device__ __forceinline__ void replay_sample(const SceneDev& sc, const RayParams& rp, float3 o, float3 d, int kq,
                                               bool act, float& a, float& tau, float* v, Corners& cn, OccValue& oc) {
     a = 0.0f;
@@ -204,7 +204,7 @@ __device__ __forceinline__ void replay_sample(const SceneDev& sc, const RayParam
         cn = corners_of<false, kNarrow>(sc, p);
         if (kSoft) oc = occ_value(sc, p, rp.occ_inv_eps);
         float t[8];
-        gather_features_split<S, kNarrow>(sc, cn, t);
+        gather_features_split<S, kNarrow, kFew>(sc, cn, t);
         tau = __expf(t[0]);
         a = tau * rp.delta;
 #pragma unroll
@@ -385,8 +385,13 @@ __device__ __forceinline__ void hand_out(unsigned int* next_ray, int64_t from, i
     }
 }
 
-template <class S, bool kSoft, bool kNarrow>
-__global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams rp, const float* __restrict__ o_,
+// kFew: a batch that leaves the chip with a wave per SIMD, or two: nothing hides
+// a wave's loads then, so a sample's texels are loaded all at once, in
+// registers that more waves would need.  Steps of 4,096 rays: 193 us with few
+// in flight and 187 so on planes of 256 x 256 texels, 526 and 501 on 2048 x
+// 2048, with everything trained 837 and 761; of 8,192 rays 543 and 516.
+template <class S, bool kSoft, bool kNarrow, bool kFew>
+__global__ __launch_bounds__(kBlock, kFew ? 2 : 4) void k_march_bwd(SceneDev sc, RayParams rp, const float* __restrict__ o_,
                                                        const float* __restrict__ d_, int64_t n,
                                                        const int32_t* __restrict__ order, const int* __restrict__ sched,
                                                        unsigned int* __restrict__ next_ray,
@@ -442,7 +447,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
                 float a, tau, v[7];
                 Corners cn;
                 OccValue oc;
-                replay_sample<S, kSoft, kNarrow>(scene_argument(), rp, o, d, kq, act, a, tau, v, cn, oc);
+                replay_sample<S, kSoft, kNarrow, kFew>(scene_argument(), rp, o, d, kq, act, a, tau, v, cn, oc);
                 const float incl = g_scan_incl(a, gl);
                 const float excl = g_shift_up1(incl);
                 const float w = act ? __expf(-(carry + excl)) * (-expm1f(-a)) * (kSoft ? oc.m : 1.0f) : 0.0f;
@@ -480,7 +485,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_bwd(SceneDev sc, RayParams 
             float a, tau, v[7];
             Corners cn;
             OccValue oc;
-            replay_sample<S, kSoft, kNarrow>(scene_argument(), rp, o, d, kq, act, a, tau, v, cn, oc);
+            replay_sample<S, kSoft, kNarrow, kFew>(scene_argument(), rp, o, d, kq, act, a, tau, v, cn, oc);
             const float incl = g_scan_incl(a, gl);
             const float excl = g_shift_up1(incl);
             const float Ti = __expf(-(carry + excl));
@@ -635,6 +640,8 @@ hipError_t launch_bwd_order(const int32_t* counts, int64_t n, int n_max, int32_t
     return hipGetLastError();
 }
 
+constexpr int64_t kFewRays = 256 * 4 * 2 * 4;  // two waves per SIMD, four rays each
+
 hipError_t launch_march_bwd(const SceneDev& sc, bool bf16, const RayParams& rp, const float* o, const float* d,
                             int64_t n, const float* T, const int32_t* n_eval, const float* batch_wv, const float* G8,
                             const int32_t* order, int* sched, const BatchRecords* br, float* gV, float* gxy,
@@ -653,13 +660,17 @@ hipError_t launch_march_bwd(const SceneDev& sc, bool bf16, const RayParams& rp, 
     typedef void (*Form)(SceneDev, RayParams, const float*, const float*, int64_t, const int32_t*, const int*,
                          unsigned int*, const float*, const int32_t*, const float*, const float*, float*, float*,
                          float*, float*, float*);
-    static constexpr Form forms[2][2][2] = {
-        {{k_march_bwd<F32Store, false, false>, k_march_bwd<F32Store, false, true>},
-         {k_march_bwd<F32Store, true, false>, k_march_bwd<F32Store, true, true>}},
-        {{k_march_bwd<BF16Store, false, false>, k_march_bwd<BF16Store, false, true>},
-         {k_march_bwd<BF16Store, true, false>, k_march_bwd<BF16Store, true, true>}}};
-    hipLaunchKernelGGL(forms[bf16][soft][narrow_scene(sc, bf16 ? OM_BF16 : OM_F32)], grid, block, 0, s, sc, rp, o, d, n,
-                       order, sched, next_ray, T, n_eval, batch_wv, G8, gV, gxy, gxz, gyz, gocc);
+    static constexpr Form forms[2][2][2][2] = {
+        {{{k_march_bwd<F32Store, false, false, false>, k_march_bwd<F32Store, false, true, false>},
+          {k_march_bwd<F32Store, true, false, false>, k_march_bwd<F32Store, true, true, false>}},
+         {{k_march_bwd<BF16Store, false, false, false>, k_march_bwd<BF16Store, false, true, false>},
+          {k_march_bwd<BF16Store, true, false, false>, k_march_bwd<BF16Store, true, true, false>}}},
+        {{{k_march_bwd<F32Store, false, false, true>, k_march_bwd<F32Store, false, true, true>},
+          {k_march_bwd<F32Store, true, false, true>, k_march_bwd<F32Store, true, true, true>}},
+         {{k_march_bwd<BF16Store, false, false, true>, k_march_bwd<BF16Store, false, true, true>},
+          {k_march_bwd<BF16Store, true, false, true>, k_march_bwd<BF16Store, true, true, true>}}}};
+    hipLaunchKernelGGL(forms[n <= kFewRays][bf16][soft][narrow_scene(sc, bf16 ? OM_BF16 : OM_F32)], grid, block, 0, s,
+                       sc, rp, o, d, n, order, sched, next_ray, T, n_eval, batch_wv, G8, gV, gxy, gxz, gyz, gocc);
     return hipGetLastError();
 }
 

@@ -370,9 +370,10 @@ __device__ __forceinline__ Corners corners_of(const SceneDev& sc, float3 p) {
 }
 
 // Eq. 2: t = trilinear(V) + bilinear(P_xy) + bilinear(P_xz) + bilinear(P_yz),
-// one lane per sample, with at most 12 corners in flight (grid first, then
-// planes), for kernels that carry more live state than the forward march.
-template <class S, bool kNarrow>
+// one lane per sample, with few corners in flight (grid first, then planes),
+// for kernels that carry more live state than the forward march; kAll: all of
+// the grid's, then all of the planes'.
+template <class S, bool kNarrow, bool kAll = false>
 __device__ __forceinline__ void gather_features_split(const SceneDev& sc, const Corners& c, float* t) {
     using A = RowAddr<kNarrow, S::kBytes>;
     const uint32_t kg = A::key(c.g), kp[3] = {A::key(c.xy), A::key(c.xz), A::key(c.yz)};
@@ -382,20 +383,21 @@ __device__ __forceinline__ void gather_features_split(const SceneDev& sc, const 
     const uint32_t nx = (uint32_t)sc.Nx, ny = (uint32_t)sc.Ny;
     // two rows (one pair adjacent along the row axis) in flight for 32-byte
     // rows, four for 16-byte rows
-    constexpr int kPerGroup = sizeof(typename S::Row) > 16 ? 1 : 2;
+    constexpr int kFew = sizeof(typename S::Row) > 16 ? 1 : 2;
+    constexpr int kGrid = kAll ? 4 : kFew, kPlane = kAll ? 6 : kFew;
     const float x0 = 1.0f - c.fx, x1 = c.fx, y0 = 1.0f - c.fy, y1 = c.fy, z0 = 1.0f - c.fz, z1 = c.fz;
 #pragma unroll
-    for (int p0 = 0; p0 < 4; p0 += kPerGroup) {
-        typename S::Row r[2 * kPerGroup];
+    for (int p0 = 0; p0 < 4; p0 += kGrid) {
+        typename S::Row r[2 * kGrid];
 #pragma unroll
-        for (int k = 0; k < kPerGroup; ++k) {
+        for (int k = 0; k < kGrid; ++k) {
             const int p = p0 + k;  // (dy, dz) = (p & 1, p >> 1)
             const char* row = A::at(sc.grid, ((p & 1) ? sy : 0u) + ((p >> 1) ? sz : 0u), kg);
             r[2 * k] = S::load(row);
             r[2 * k + 1] = S::load(row + S::kBytes);
         }
 #pragma unroll
-        for (int k = 0; k < kPerGroup; ++k) {
+        for (int k = 0; k < kGrid; ++k) {
             const int p = p0 + k;
             const float wyz = ((p & 1) ? y1 : y0) * ((p >> 1) ? z1 : z0);
             S::acc(r[2 * k], x0 * wyz, t);
@@ -404,10 +406,10 @@ __device__ __forceinline__ void gather_features_split(const SceneDev& sc, const 
     }
     const float a0 = 1.0f - c.ux, a1 = c.ux, b0 = 1.0f - c.uy, b1 = c.uy, e0 = 1.0f - c.uz, e1 = c.uz;
 #pragma unroll
-    for (int p0 = 0; p0 < 6; p0 += kPerGroup) {
-        typename S::Row r[2 * kPerGroup];
+    for (int p0 = 0; p0 < 6; p0 += kPlane) {
+        typename S::Row r[2 * kPlane];
 #pragma unroll
-        for (int k = 0; k < kPerGroup; ++k) {
+        for (int k = 0; k < kPlane; ++k) {
             const int p = p0 + k;  // plane p >> 1, second-axis offset p & 1
             const int q = p >> 1;
             const void* P = q == 0 ? sc.pxy : q == 1 ? sc.pxz : sc.pyz;
@@ -416,7 +418,7 @@ __device__ __forceinline__ void gather_features_split(const SceneDev& sc, const 
             r[2 * k + 1] = S::load(row + S::kBytes);
         }
 #pragma unroll
-        for (int k = 0; k < kPerGroup; ++k) {
+        for (int k = 0; k < kPlane; ++k) {
             const int p = p0 + k;
             const int q = p >> 1;
             const float u0 = q == 2 ? b0 : a0, u1 = q == 2 ? b1 : a1;
