@@ -152,6 +152,7 @@ int validate_desc(const om_scene_desc* d, SceneDev* out) {
         }
         s.qlo[c] = (float)lo;
     }
+    for (int i = 0; i < 4; ++i) s.qlo0[i] = d->dtype == OM_U8 ? d->quant_lo[i][0] : 0.0f;
     s.Lx = d->grid_dims[0];
     s.Ly = d->grid_dims[1];
     s.Lz = d->grid_dims[2];

@@ -140,7 +140,8 @@ __device__ __forceinline__ void store_group_total(float x, int gl, float* dst) {
 // bound by vector instructions: reading the decoding from the argument
 // segment instead of spilled scalar registers, and one offset per channel
 // instead of four, took a 1920x1080 frame with sparse blocks and early
-// termination from 3.78 to 2.97 ms.  bfloat16 is bound by L1 line lookups
+// termination from 3.78 to 2.97 ms (2.52 with xcd_block's runs).  bfloat16 is
+// bound by L1 line lookups
 // (1.19 per clock, 36 per load instruction).
 // ---------------------------------------------------------------------------
 // A sample as the lane that owns it holds it for the other lanes of its quad.
@@ -371,8 +372,9 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarr
 // contiguous bytes, so each gather instruction reads one 64-byte span for
 // each of 4 consecutive samples of the ray.
 //
-// The kernel is bound by vector instruction issue (a wave64 instruction takes
-// a SIMD 4 cycles), so whatever a sample needs once is computed on one lane:
+// A load instruction moves 1,024 bytes, 16 cycles of the L1 at 64 bytes each;
+// the kernel starts one every 18.7, with vector instructions in 87 % of the
+// cycles.  So whatever a sample needs once is computed on one lane:
 // lane 4s + j holds sample 4j + s from the start -- its point, row offsets and
 // fractions, density, optical depth and weight -- and hands it to the quad
 // that shades it with DPP quad broadcasts, which cost one instruction or ride
@@ -380,8 +382,8 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarr
 // end with two channels each, so an activation is evaluated once.  With all
 // of that on all four lanes, 64-bit vector addresses and scalar registers
 // spilled to vector lanes, 64 samples took 1240 vector instructions and a
-// 1920x1080 frame of the full-size scene 13.98 ms; now some 600 and 10.52 ms,
-// with the L1 looking up 0.9 lines per clock.
+// 1920x1080 frame of the full-size scene 13.98 ms; with some 600 10.52 ms, and
+// 9.14 with the rays dealt to the XCDs in short runs (xcd_block).
 // ---------------------------------------------------------------------------
 // Sample 4j + s of the quad, j = kJ: the lane's half of the channels, summed
 // over the rows at its x-offset.  lane_off: the lane's 16 bytes within a
@@ -476,17 +478,15 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
         quarter(std::integral_constant<int, 3>{});
         const bool act = pos < nb;
         const float a = act ? __expf(t0) * rp.delta : 0.0f;
-        // Optical depth in front of the lane's sample: carry + the samples
-        // of earlier quarters (lanes of lower q) + those before it in its own
-        // quarter (lower quads, same q).
+        // Optical depth in front of the lane's sample: carry + the earlier
+        // quarters one after another (their totals are in the last quad) +
+        // the samples before it in its own quarter (lower quads, same q).
         float col = a;
         col += dpp_row<kRowShr | 4>(col);
         col += dpp_row<kRowShr | 8>(col);
-        float quart = gl >= 12 ? col : 0.0f;  // quarter totals, in the last quad
-        quart += dpp_row<kRowShr | 1>(quart);
-        quart += dpp_row<kRowShr | 2>(quart);
-        const float pre = carry + quad_column_sum(g_shift_up1(quart)) + dpp_row<kRowShr | 4>(col);
-        const float total = row_bcast<kGroup - 1>(quart);
+        const float run1 = carry + row_bcast<12>(col), run2 = run1 + row_bcast<13>(col), run3 = run2 + row_bcast<14>(col);
+        const float run = q == 0 ? carry : q == 1 ? run1 : q == 2 ? run2 : run3;
+        const float pre = run + dpp_row<kRowShr | 4>(col);
         int nb_eff = nb;
         bool stop = false;
         if (rp.t_term > 0.0f) {
@@ -533,7 +533,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
         ++batch;
         // depth through the last evaluated sample
         const int last = nb_eff - 1;
-        carry = stop ? __shfl(pre + a, 4 * (last & 3) + (last >> 2), kGroup) : carry + total;
+        carry = nb_eff == kGroup ? row_bcast<kGroup - 1>(pre + a)
+                                 : __shfl(pre + a, 4 * (last & 3) + (last >> 2), kGroup);
         evals += nb_eff;
         return stop;
     });
