@@ -439,11 +439,11 @@ def fwd_bwd_l2_workspace_size(n: int, n_max: int, delta: float = DELTA) -> int:
     return nb
 
 
-def fwd_bwd_l2_records_size(scene: Scene, n: int, n_max: int) -> int:
+def fwd_bwd_l2_records_size(scene: Scene, n: int, n_max: int, delta: float = DELTA) -> int:
     """Bytes beyond fwd_bwd_l2_workspace_size(n, n_max) with which the fused
     step of a large batch keeps batch records for its backward
     (om_render_fwd_bwd_l2_records_size); 0 where that does not pay."""
-    p = _params(n_max, DELTA, 0.0, (0.0, 0.0, 0.0), -1)
+    p = _params(n_max, delta, 0.0, (0.0, 0.0, 0.0), -1)
     nb = _lib.lib().om_render_fwd_bwd_l2_records_size(scene.handle, n, ctypes.byref(p))
     if nb < 0:
         raise _lib.OmerfError("om_render_fwd_bwd_l2_records_size", _lib.OM_ERR_INVALID,
@@ -451,10 +451,10 @@ def fwd_bwd_l2_records_size(scene: Scene, n: int, n_max: int) -> int:
     return int(nb)
 
 
-def _fwd_bwd_l2_workspace(scene: Scene, n: int, n_max: int, nbytes: int) -> torch.Tensor:
+def _fwd_bwd_l2_workspace(scene: Scene, n: int, n_max: int, delta: float, nbytes: int) -> torch.Tensor:
     """A workspace for the fused step, with room for the batch records where
     they help and the device has that much memory left."""
-    records = fwd_bwd_l2_records_size(scene, n, n_max)
+    records = fwd_bwd_l2_records_size(scene, n, n_max, delta)
     if records > 0:
         try:
             return torch.empty((nbytes + records,), dtype=torch.uint8, device=scene.device)
@@ -470,15 +470,16 @@ def render_fwd_bwd_l2(scene: Scene, o, d, target, out: Dict[str, torch.Tensor], 
     """One fused L2 training step (om_render_fwd_bwd_l2): forward into `out`
     (keys as render()), dL/dC, the loss into `loss` (a device float32 [1]
     tensor, or None to skip), and the backward ADDED into float32 `grads`.
-    `workspace` is a device uint8 tensor of fwd_bwd_l2_workspace_size bytes
-    (allocated here if None)."""
+    `workspace` is a device uint8 tensor of fwd_bwd_l2_workspace_size bytes;
+    one that is larger by fwd_bwd_l2_records_size makes a large batch faster
+    (allocated here if None, with those where the memory is there)."""
     n = _rays(scene, o, d)
     _need(target, "target", torch.float32, (n, 3))
     for key in ("grid", "plane_xy", "plane_xz", "plane_yz", "mlp"):
         _need(grads[key], f"grads[{key}]", torch.float32, scene.tensors[key].shape)
     nbytes = fwd_bwd_l2_workspace_size(n, n_max, delta)
     if workspace is None:
-        workspace = _fwd_bwd_l2_workspace(scene, n, n_max, nbytes)
+        workspace = _fwd_bwd_l2_workspace(scene, n, n_max, delta, nbytes)
     _need_workspace(workspace, nbytes, o.device)
     if loss is not None:
         _need(loss, "loss", torch.float32, (1,))

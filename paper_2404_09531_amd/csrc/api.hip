@@ -432,7 +432,7 @@ hipError_t backward_launch(const om_scene* scene, const RayParams& rp, const flo
 // fit whole.
 void* records_part(const om_scene* scene, int64_t n, const RayParams& rp, void* workspace, int64_t bytes, int64_t need) {
     const int64_t at = (need + 255) / 256 * 256;
-    const int64_t more = record_workspace(scene->dev, n, rp.n_max, nullptr, nullptr, nullptr);
+    const int64_t more = record_workspace(scene->dev, rp, n, nullptr, nullptr, nullptr);
     return more > 0 && bytes - at >= more ? static_cast<char*>(workspace) + at : nullptr;
 }
 
@@ -469,7 +469,7 @@ int64_t om_render_fwd_bwd_l2_records_size(const om_scene* scene, int64_t n, cons
     }
     if (validate_params(p, &rp) != OM_OK) return -1;
     if (n == 0 || scene->desc.dtype == OM_U8 || scene->desc.block_shift > 0) return 0;
-    const int64_t more = record_workspace(scene->dev, n, rp.n_max, nullptr, nullptr, nullptr);
+    const int64_t more = record_workspace(scene->dev, rp, n, nullptr, nullptr, nullptr);
     return more > 0 ? more + 256 : 0;
 }
 
@@ -528,7 +528,7 @@ int fwd_bwd_l2_launch(const om_scene* scene, const float* o, const float* d, int
     const BatchRecords* brp = nullptr;
     hipError_t e = hipSuccess;
     if (records) {
-        record_workspace(scene->dev, n, rp.n_max, records, &br, &tl);
+        record_workspace(scene->dev, rp, n, records, &br, &tl);
         brp = &br;
         e = launch_order_rays(scene->desc.box_lo, scene->desc.box_hi, o, d, n, br.ray_at, nullptr, nullptr, br.hist,
                               br.keys, s);

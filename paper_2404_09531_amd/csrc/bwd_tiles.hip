@@ -310,14 +310,15 @@ namespace {
 constexpr int64_t align256(int64_t b) { return (b + 255) / 256 * 256; }
 }  // namespace
 
-int64_t record_workspace(const SceneDev& sc, int64_t n, int n_max, void* base, BatchRecords* br, TileLists* tl) {
+int64_t record_workspace(const SceneDev& sc, const RayParams& rp, int64_t n, void* base, BatchRecords* br,
+                         TileLists* tl) {
     // At most 6 Mi records (4.5 GB): rays take them longest first, and what is
     // left replays its samples.
-    const int64_t batches = n * ((n_max + kGroup - 1) / kGroup);
+    const int64_t batches = n * ((rp.n_max + kGroup - 1) / kGroup);
     const int64_t cap = batches < (6ll << 20) ? batches : (6ll << 20);
     const int64_t nu_x = (sc.Nx - 2) / kTileU + 1, nu_y = (sc.Ny - 2) / kTileU + 1, nv = (sc.Nz - 2) / kTileV + 1;
     const int64_t bins = (nu_x + nu_y) * nv;
-    if (batches <= kRecordBatches || bins > kTileMaxBins) return 0;
+    if (batches <= kRecordBatches || bins > kTileMaxBins || texels_per_step(sc, rp.delta) < kRecordTexels) return 0;
     const int64_t parts[9] = {cap * kRecFloats * (int64_t)sizeof(float),
                               n * (int64_t)sizeof(int32_t),
                               cap * kKeysPerBatch * (int64_t)sizeof(uint16_t),

@@ -594,11 +594,7 @@ bool narrow_scene(const SceneDev& sc, int dtype) {
            (uint64_t)sc.Nx * (uint64_t)sc.Nz * bytes <= most && (uint64_t)sc.Ny * (uint64_t)sc.Nz * bytes <= most;
 }
 
-// Whether a step crosses 0.15 of a plane texel or more on every axis: where it
-// crosses less, the samples of a quad share their rows anyway (GatherBF16Lds).
-static bool fine_planes(const SceneDev& sc, float delta) {
-    return fminf(sc.px.s, fminf(sc.py.s, sc.pz.s)) * delta >= 0.15f;
-}
+float texels_per_step(const SceneDev& sc, float delta) { return fminf(sc.px.s, fminf(sc.py.s, sc.pz.s)) * delta; }
 
 template <bool kSoft, bool kSparse, bool kNarrow>
 static void launch_fwd_form(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
@@ -620,7 +616,8 @@ static void launch_fwd_form(const SceneDev& sc, int dtype, const RayParams& rp, 
     static constexpr Kernel bf16_lds =
         k_march_fwd_lane<std::conditional_t<kLds, GatherBF16Lds, GatherBF16>, kSaveNone, kSoft, kSparse, kNarrow>;
     const int save = br ? kSaveRecords : batch_wv ? kSaveSums : kSaveNone;
-    const bool lds = kLds && save == kSaveNone && fine_planes(sc, rp.delta);
+    // Below 0.15 texels per step the samples of a quad share their rows anyway.
+    const bool lds = kLds && save == kSaveNone && texels_per_step(sc, rp.delta) >= 0.15f;
     const Kernel k = dtype == OM_U8 ? k_march_fwd_lane<GatherU8, kSaveNone, kSoft, kSparse, kNarrow>
                                     : dtype == OM_BF16 ? (lds ? bf16_lds : bf16[save]) : f32[save];
     hipLaunchKernelGGL(k, dim3(blocks_for(n)), dim3(kBlock), 0, s, sc, rp, o, d, n, F, T, n_placed, n_eval, batch_wv,

@@ -30,8 +30,14 @@ constexpr int kRecPoint = 8 * kGroup, kRecCarry = 11 * kGroup, kRecFloats = 12 *
 // 1.83 and 1.78 ms, 637,000 (of 2^20) 3.29 and 3.43, 1.27 million 5.7 and 6.4,
 // 2.54 million 10.4 and 12.3, 5.1 million in bfloat16 18.9 and 23.0; below, the
 // planes' tiles are too thinly covered to pay for their sums (212,000: 1.22 and
-// 1.07).
+// 1.07).  And only where a step crosses 0.4 of a plane's texel or more on every
+// axis: on coarser planes a batch touches few texels and the scatter is cheap.
+// 104,487 rays in float32 and bfloat16: planes of 3072 x 3069 texels 4.14 and
+// 4.58 ms, 3.91 and 4.28; 2048 3.48 and 3.77, 3.23 and 3.36; 1536 3.28 and
+// 3.37, 3.04 and 3.02; 700 2.83 and 2.72, 2.65 and 2.46; 359 2.75 and 2.50,
+// 2.60 and 2.32.
 constexpr int64_t kRecordBatches = 1 << 20, kRecordMin = 1 << 19;
+constexpr float kRecordTexels = 0.4f;
 struct BatchRecords {
     float* rec;
     int32_t* slot_of_ray;  // [n] first record of each ray, -1: none
@@ -46,6 +52,8 @@ __host__ __device__ constexpr int record_place(int i) { return 4 * (i & 3) + (i 
 
 // br: NULL, or the records; rays without one get the per-batch sums.
 // n_placed then holds the placement counts on entry (launch_count).
+// Texels of a plane that a step crosses at most, of the axis with the fewest.
+float texels_per_step(const SceneDev& sc, float delta);
 hipError_t launch_march_fwd(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
                             int64_t n, float* F, float* T, int32_t* n_placed, int32_t* n_eval, float* batch_wv,
                             const BatchRecords* br, hipStream_t s);
@@ -83,7 +91,8 @@ struct TileLists {
 };
 // Workspace bytes of the records and lists for n rays of at most n_max
 // samples, or 0 where they do not pay; fills *br and *tl when base is non-NULL.
-int64_t record_workspace(const SceneDev& sc, int64_t n, int n_max, void* base, BatchRecords* br, TileLists* tl);
+int64_t record_workspace(const SceneDev& sc, const RayParams& rp, int64_t n, void* base, BatchRecords* br,
+                         TileLists* tl);
 hipError_t launch_tile_sums(const SceneDev& sc, const BatchRecords& br, const TileLists& tl, const int* records,
                             float* gxz, float* gyz, hipStream_t s);
 hipError_t launch_mlp_bwd(const float* W, int mlp_in, const RayParams& rp, const float* F, const float* d,

@@ -2,9 +2,10 @@
 sums, against the same step in the smallest workspace, which replays.
 
 Records are kept from 2^20 possible and 2^19 placed batches on, 6 x 2^20 of
-them at most; the XZ and YZ gradients are summed in tiles of 17 x 20 base
-texels, of which a batch is listed under four per plane.  The planes below end
-at a tile's edge, one texel behind it, and inside the first tile.
+them at most, where a step crosses 0.4 texels of the planes (1,640 x 1,640 x
+206 with steps of 1/2048); the XZ and YZ gradients are summed in tiles of 17 x
+20 base texels, of which a batch is listed under four per plane.  The planes
+below end at a tile's edge, one texel behind it, and in between.
 
 Bar: counts equal; C, F and T, whose arithmetic is the same up to the
 compiler's choice of fused multiply-adds, within the 1e-5 that each is held to
@@ -24,6 +25,7 @@ pytestmark = pytest.mark.gpu
 
 KEYS = ("grid", "plane_xy", "plane_xz", "plane_yz", "mlp")
 BG = (0.25, 0.5, 0.75)
+FINE = (1700, 1660, 210)
 
 
 class Step:
@@ -37,7 +39,7 @@ class Step:
         g.manual_seed(7)
         self.target = torch.rand(self.n, 3, device=DEV, generator=g)
         self.need = om.fwd_bwd_l2_workspace_size(self.n, kw["n_max"])
-        self.records = om.fwd_bwd_l2_records_size(self.scene, self.n, kw["n_max"])
+        self.records = om.fwd_bwd_l2_records_size(self.scene, self.n, kw["n_max"], kw.get("delta", om.DELTA))
 
     def buffers(self):
         e = lambda *s, dt=torch.float32: torch.empty(s, dtype=dt, device=DEV)  # noqa: E731
@@ -82,13 +84,13 @@ def oblique(n):
 @pytest.mark.parametrize("t_term,occ_eps", [(0.0, 0.0), (1e-2, 0.0), (0.0, 0.02), (1e-2, 0.02)])
 def test_forms(dtype, t_term, occ_eps):
     log(f"test_forms: {dtype}, t_term {t_term}, occ_eps {occ_eps}")
-    sc = micro_scene(grid=(20, 18, 9), planes=(40, 30, 45), m=8, zmin=0.01, zmax=0.24, seed=5)
+    sc = micro_scene(grid=(20, 18, 9), planes=FINE, m=8, zmin=0.01, zmax=0.24, seed=5)
     s = Step(sc, *oblique(70001), dtype=dtype, occ=occ_eps > 0, n_max=256, t_term=t_term, occ_eps=occ_eps)
     assert s.records > 0
     assert_same(*s.both())
 
 
-@pytest.mark.parametrize("planes", [(2, 2, 2), (18, 35, 21), (19, 36, 22), (35, 52, 41), (300, 17, 64)])
+@pytest.mark.parametrize("planes", [(1701, 1701, 221), (1702, 1701, 222), (1650, 1719, 241)])
 def test_tile_edges(planes):
     log(f"test_tile_edges: planes {planes}")
     s = Step(micro_scene(grid=(5, 6, 3), planes=planes, m=4, seed=6), *oblique(66003), n_max=256)
@@ -115,7 +117,7 @@ def test_batches_across_many_tiles():
 @pytest.mark.parametrize("n,zmax", [(70001, 0.02), ((1 << 20) + 3, 0.25)])
 def test_few_batches_and_more_than_the_records(n, zmax):
     log(f"test_few_batches_and_more_than_the_records: {n} rays, occupied up to {zmax}")
-    s = Step(micro_scene(grid=(20, 18, 9), planes=(40, 30, 45), m=8, zmax=zmax, seed=5), *oblique(n), n_max=256)
+    s = Step(micro_scene(grid=(20, 18, 9), planes=FINE, m=8, zmax=zmax, seed=5), *oblique(n), n_max=256)
     assert s.records > 0
     plain, recorded = s.both()
     batches = int(((plain[0]["n_placed"] + 15) // 16).sum())
@@ -127,7 +129,7 @@ def test_workspace_rules():
     """One byte less than the records need is the smallest workspace's step;
     no workspace takes the records; small batches have none."""
     log("test_workspace_rules")
-    sc = micro_scene(grid=(20, 18, 9), planes=(40, 30, 45), m=8, seed=5)
+    sc = micro_scene(grid=(20, 18, 9), planes=FINE, m=8, seed=5)
     s = Step(sc, *oblique(66003), n_max=256)
     ref = s.buffers()
     s.run(*ref, s.need)
@@ -140,6 +142,7 @@ def test_workspace_rules():
     assert_same(ref, got)
     sizes = [om.fwd_bwd_l2_records_size(s.scene, n, 256) for n in (0, 1, 65536, 65537)]
     assert sizes[:3] == [0, 0, 0] and sizes[3] > 0
+    assert om.fwd_bwd_l2_records_size(s.scene, 65537, 256, om.DELTA / 2) == 0
     with pytest.raises(om.OmerfError):
         om.fwd_bwd_l2_records_size(s.scene, -1, 256)
     with pytest.raises(om.OmerfError):
@@ -148,7 +151,7 @@ def test_workspace_rules():
 
 def test_capture():
     log("test_capture")
-    sc = micro_scene(grid=(20, 18, 9), planes=(40, 30, 45), m=8, seed=5)
+    sc = micro_scene(grid=(20, 18, 9), planes=FINE, m=8, seed=5)
     s = Step(sc, *oblique(66003), n_max=256)
     want = s.buffers()
     s.run(*want, s.need + s.records)
