@@ -61,7 +61,7 @@ def parse():
 # figure is used only while the hash of its family's files is unchanged.
 KERNEL_SOURCES = {
     "fwd": ("omerf_device.h", "march_fwd.hip"),
-    "bwd": ("omerf_device.h", "bwd_device.h", "march_bwd.hip"),
+    "bwd": ("omerf_device.h", "bwd_device.h", "march_bwd.hip", "bwd_tiles.hip"),
     "mlp": ("omerf_device.h", "mlp.hip"),
 }
 
