@@ -532,7 +532,7 @@ __global__ __launch_bounds__(kBlock, kFew ? 2 : 4) void k_march_bwd(SceneDev sc,
 // rays in float32 in 4.5 ms, near the 20.6 G/s that they reach beyond L2
 //.  The step took 12.3 ms with
 // the samples replayed and four sources scattered; the rays' order (0.09), their
-// counts (0.23), the forward with records (2.6), this and the tiles' sums (2.9)
+// counts (0.18), the forward with records (2.6), this and the tiles' sums (2.9)
 // take 10.4.
 // ---------------------------------------------------------------------------
 struct RecordLoad {

@@ -43,15 +43,12 @@ __global__ __launch_bounds__(kBlock) void k_place(SceneDev sc, RayParams rp, con
 __global__ __launch_bounds__(kBlock) void k_count(SceneDev sc, RayParams rp, const float* __restrict__ o_,
                                                   const float* __restrict__ d_, int64_t n,
                                                   const int32_t* __restrict__ ray_at, int32_t* __restrict__ n_placed) {
-    __shared__ int qs[kGroupsPerBlock][kQueue];
     const int lane = threadIdx.x & 63;
     const int gl = lane & (kGroup - 1);
-    const int gid = threadIdx.x / kGroup;
-    const int64_t at = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGroupsPerBlock + gid;
+    const int64_t at = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kGroupsPerBlock + threadIdx.x / kGroup;
     if (at >= n) return;
     const int64_t ray = ray_at[at];
-    const int cnt = march_candidates(sc, rp, load3(o_, ray), load3(d_, ray), qs[gid], gl, gl, lane,
-                                     [](int, int) { return false; });
+    const int cnt = count_candidates(sc, rp, load3(o_, ray), load3(d_, ray), gl, lane);
     if (gl == 0) n_placed[ray] = cnt;
 }
 
