@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kListThreads) void k_tile_keys(SceneDev sc, const f
     for (int i = s + (int)threadIdx.x / kGroup; i < e; i += kListThreads / kGroup) {
         const float* r = recs + (size_t)i * kRecFloats;
         const float px = r[kRecPoint + gl], py = r[kRecPoint + kGroup + gl], pz = r[kRecPoint + 2 * kGroup + gl];
-        const bool add = px == px;
+        const bool add = pz == pz;
         int mine = kNoTile;
         batch_tiles(r, gxz, 0, tl.nu_x, sc.px, sc.pz, px, pz, add, 0, gl, lane, mine);
         batch_tiles(r, gyz, tl.yz, tl.nu_y, sc.py, sc.pz, py, pz, add, kTileKeys, gl, lane, mine);
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64) void k_tile_sum(SceneDev sc, const float* __res
                 axis_coord(t.pv, mv, iv, fv);
                 iu -= u0;
                 iv -= w0;
-                const bool in = t.pu == t.pu && (unsigned)iu < (unsigned)kTileU && (unsigned)iv < (unsigned)kTileV;
+                const bool in = t.pv == t.pv && (unsigned)iu < (unsigned)kTileU && (unsigned)iv < (unsigned)kTileV;
                 const uint32_t off = in ? (uint32_t)(iv * kTilePitch + iu * 8) : (uint32_t)kTileFloats;
                 const float w = fmaf(hs, fu, h0) * fmaf(vs, fv, v0);
                 const int key = in ? iv * 64 + iu : (100 + 4 * lane) * 64;

@@ -611,7 +611,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_grad(SceneDev sc, RayParams rp, c
                 r[c * kGroup] = gt[c];
                 add |= gt[c] != 0.0f;
             }
-            if (!(add && act)) r[kRecPoint] = __uint_as_float(0x7fc00000u);
+            if (!(add && act)) r[kRecPoint + 2 * kGroup] = __uint_as_float(0x7fc00000u);
             Corners cn{};  // defined keys and weights on inactive lanes, which the group scans read
             if (act) cn = corners_of(scene_argument(), p);
             scatter_batch_runs<false>(scene_argument(), gV, gxy, nullptr, nullptr, stage, act, cn, gt, gl, lane);

@@ -64,7 +64,7 @@ enum { kSaveNone, kSaveSums, kSaveRecords };
 // termination), as without samples.
 __device__ __forceinline__ void clear_records(const BatchRecords& br, int slot, int batch, int slots, int gl) {
     for (; batch < slots; ++batch)
-        br.rec[(size_t)(slot + batch) * kRecFloats + kRecPoint + gl] = __uint_as_float(0x7fc00000u);
+        br.rec[(size_t)(slot + batch) * kRecFloats + kRecPoint + 2 * kGroup + gl] = __uint_as_float(0x7fc00000u);
 }
 
 // ---------------------------------------------------------------------------

@@ -21,7 +21,8 @@ hipError_t launch_mark(const SceneDev& sc, const RayParams& rp, const float* o, 
 //   [0, 128)    [8][16]: channel 0 the samples' optical depths, 1..7 their
 //               activated features, from the forward in record_place order;
 //               then dL/dt of the 8 channels, in sample order, from k_grad
-//   [128, 176)  [3][16]: the sample points (x NaN: nothing to add)
+//   [128, 176)  [3][16]: the sample points (z, which both the XZ and the YZ sums
+//               read, NaN: nothing to add)
 //   176         the optical depth in front of the batch
 constexpr int kRecPoint = 8 * kGroup, kRecCarry = 11 * kGroup, kRecFloats = 12 * kGroup;
 // A fused step keeps records where n rays of at most n_max samples may have
