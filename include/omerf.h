@@ -224,7 +224,9 @@ int om_scene_update(om_scene* scene, const om_scene_desc* desc);
  * call skips empty space level by level.  Sample placement is unchanged
  * (the pyramid only skips candidates that cannot be accepted).  levels = 0
  * detaches it; so does om_scene_update, after which it must be built again
- * for the new occupancy.  Must not race with calls using the handle.
+ * for the new occupancy, as after a change of the plane in place (a pyramid of
+ * an older plane makes calls skip samples that lie in its empty blocks).  Must
+ * not race with calls using the handle.
  */
 int64_t om_occupancy_mips_size(const om_scene* scene, int levels);
 int om_build_occupancy_mips(om_scene* scene, void* mips, int64_t mips_bytes, int levels, void* stream);
