@@ -400,10 +400,11 @@ int64_t om_render_fwd_bwd_l2_workspace_size(int64_t n, const om_params* p);
  * stay in the caller's), keeps a record per 16-sample batch between the forward
  * and the backward, instead of replaying the samples, and sums the XZ and YZ
  * gradients by tiles instead of one float atomic per segment: bytes to add (p:
- * only n_max and delta are read), 0 where that would not pay for this scene and batch, -1
- * (with om_last_error set) on invalid arguments.  A call whose workspace holds
- * them uses them; with a smaller one it computes the same without.  At most
- * about 5 GB; batches with more samples keep the records of their longest rays.
+ * n_max, delta and t_term are read), 0 where that would not pay for this scene
+ * and batch (always with early termination, t_term > 0), -1 (with om_last_error
+ * set) on invalid arguments.  A call whose workspace holds them uses them; with
+ * a smaller one it computes the same without.  At most about 5 GB; batches with
+ * more samples keep the records of their longest rays.
  */
 int64_t om_render_fwd_bwd_l2_records_size(const om_scene* scene, int64_t n, const om_params* p);
 

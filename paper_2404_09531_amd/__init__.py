@@ -439,11 +439,12 @@ def fwd_bwd_l2_workspace_size(n: int, n_max: int, delta: float = DELTA) -> int:
     return nb
 
 
-def fwd_bwd_l2_records_size(scene: Scene, n: int, n_max: int, delta: float = DELTA) -> int:
+def fwd_bwd_l2_records_size(scene: Scene, n: int, n_max: int, delta: float = DELTA, t_term: float = 0.0) -> int:
     """Bytes beyond fwd_bwd_l2_workspace_size(n, n_max) with which the fused
     step of a large batch keeps batch records for its backward
-    (om_render_fwd_bwd_l2_records_size); 0 where that does not pay."""
-    p = _params(n_max, delta, 0.0, (0.0, 0.0, 0.0), -1)
+    (om_render_fwd_bwd_l2_records_size); 0 where that does not pay, and with
+    early termination."""
+    p = _params(n_max, delta, t_term, (0.0, 0.0, 0.0), -1)
     nb = _lib.lib().om_render_fwd_bwd_l2_records_size(scene.handle, n, ctypes.byref(p))
     if nb < 0:
         raise _lib.OmerfError("om_render_fwd_bwd_l2_records_size", _lib.OM_ERR_INVALID,
@@ -451,10 +452,11 @@ def fwd_bwd_l2_records_size(scene: Scene, n: int, n_max: int, delta: float = DEL
     return int(nb)
 
 
-def _fwd_bwd_l2_workspace(scene: Scene, n: int, n_max: int, delta: float, nbytes: int) -> torch.Tensor:
+def _fwd_bwd_l2_workspace(scene: Scene, n: int, n_max: int, delta: float, t_term: float,
+                          nbytes: int) -> torch.Tensor:
     """A workspace for the fused step, with room for the batch records where
     they help and the device has that much memory left."""
-    records = fwd_bwd_l2_records_size(scene, n, n_max, delta)
+    records = fwd_bwd_l2_records_size(scene, n, n_max, delta, t_term)
     if records > 0:
         try:
             return torch.empty((nbytes + records,), dtype=torch.uint8, device=scene.device)
@@ -479,7 +481,7 @@ def render_fwd_bwd_l2(scene: Scene, o, d, target, out: Dict[str, torch.Tensor], 
         _need(grads[key], f"grads[{key}]", torch.float32, scene.tensors[key].shape)
     nbytes = fwd_bwd_l2_workspace_size(n, n_max, delta)
     if workspace is None:
-        workspace = _fwd_bwd_l2_workspace(scene, n, n_max, delta, nbytes)
+        workspace = _fwd_bwd_l2_workspace(scene, n, n_max, delta, t_term, nbytes)
     _need_workspace(workspace, nbytes, o.device)
     if loss is not None:
         _need(loss, "loss", torch.float32, (1,))

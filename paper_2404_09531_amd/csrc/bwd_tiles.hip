@@ -318,7 +318,9 @@ int64_t record_workspace(const SceneDev& sc, const RayParams& rp, int64_t n, voi
     const int64_t cap = batches < (6ll << 20) ? batches : (6ll << 20);
     const int64_t nu_x = (sc.Nx - 2) / kTileU + 1, nu_y = (sc.Ny - 2) / kTileU + 1, nv = (sc.Nz - 2) / kTileV + 1;
     const int64_t bins = (nu_x + nu_y) * nv;
-    if (batches <= kRecordBatches || bins > kTileMaxBins || texels_per_step(sc, rp.delta) < kRecordTexels) return 0;
+    if (rp.t_term > 0.0f || batches <= kRecordBatches || bins > kTileMaxBins ||
+        texels_per_step(sc, rp.delta) < kRecordTexels)
+        return 0;
     const int64_t parts[9] = {cap * kRecFloats * (int64_t)sizeof(float),
                               n * (int64_t)sizeof(int32_t),
                               cap * kKeysPerBatch * (int64_t)sizeof(uint16_t),

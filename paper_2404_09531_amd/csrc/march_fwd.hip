@@ -60,13 +60,6 @@ __global__ __launch_bounds__(kBlock) void k_count(SceneDev sc, RayParams rp, con
 // costs.
 enum { kSaveNone, kSaveSums, kSaveRecords };
 
-// Marks the ray's records from `batch` on, which it did not reach (early
-// termination), as without samples.
-__device__ __forceinline__ void clear_records(const BatchRecords& br, int slot, int batch, int slots, int gl) {
-    for (; batch < slots; ++batch)
-        br.rec[(size_t)(slot + batch) * kRecFloats + kRecPoint + 2 * kGroup + gl] = __uint_as_float(0x7fc00000u);
-}
-
 // ---------------------------------------------------------------------------
 // Rows read by a render: for every evaluated sample (the first n_eval placed
 // samples of the ray, or all placed samples without n_eval), a byte 1 is
@@ -288,7 +281,6 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarr
     int evals = 0, batch = 0;
     const int slots = (rp.n_max + kGroup - 1) / kGroup;
     const int slot = kSave == kSaveRecords ? br.slot_of_ray[ray] : -1;
-    const int alloc = kSave == kSaveRecords ? (n_placed[ray] + kGroup - 1) / kGroup : 0;
     const int placed = march_candidates(sc, rp, o, d, qs[gid], gl, gl, lane, [&](int kq, int nb) {
         const bool act = gl < nb;
         float t[8];
@@ -348,7 +340,6 @@ __global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarr
         ++batch;
         return stop;
     });
-    if (kSave == kSaveRecords && slot >= 0) clear_records(br, slot, batch, alloc, gl);
     float f[7];
 #pragma unroll
     for (int c = 0; c < 7; ++c) f[c] = g_sum(acc[c]);
@@ -448,7 +439,6 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
     int evals = 0, batch = 0;
     const int slots = (rp.n_max + kGroup - 1) / kGroup;
     const int slot = kSave == kSaveRecords ? br.slot_of_ray[ray] : -1;
-    const int alloc = kSave == kSaveRecords ? (n_placed[ray] + kGroup - 1) / kGroup : 0;
     const int placed = march_candidates(sc, rp, o, d, qs[gid], gl, pos, lane, [&](int kq, int nb) {
         const QuadSample own = quad_sample<kNarrow, 32>(
             corners_of<kSparse, kNarrow>(scene_argument(), lattice_point(kq, o, d, rp.delta)));
@@ -535,7 +525,6 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
         evals += nb_eff;
         return stop;
     });
-    if (kSave == kSaveRecords && slot >= 0) clear_records(br, slot, batch, alloc, gl);
     acc0 = quad_column_sum(acc0);
     acc1 = quad_column_sum(acc1);
     if (gl < 4) {

@@ -36,7 +36,12 @@ constexpr int kRecPoint = 8 * kGroup, kRecCarry = 11 * kGroup, kRecFloats = 12 *
 // 104,487 rays in float32 and bfloat16: planes of 3072 x 3069 texels 4.14 and
 // 4.58 ms, 3.91 and 4.28; 2048 3.48 and 3.77, 3.23 and 3.36; 1536 3.28 and
 // 3.37, 3.04 and 3.02; 700 2.83 and 2.72, 2.65 and 2.46; 359 2.75 and 2.50,
-// 2.60 and 2.32.
+// 2.60 and 2.32.  And only without early termination: a ray's records are handed
+// out for the samples that it places, a replay is over the samples that it
+// reaches.  2^18 rays in float32 that stop at T < 1e-4 / 1e-3 / 1e-2 / 0.1 (918,000
+// to 768,000 of 1,116,000 to 966,000 batches evaluated) 5.43 and 5.08, 5.42 and
+// 4.90, 5.26 and 4.66, 4.72 and 4.23 ms; 2^20 of the towers in bfloat16 at 1e-4 /
+// 1e-2 (1,096,000 of 1,892,000, 881,000 of 1,678,000) 6.46 and 6.03, 5.57 and 5.08.
 constexpr int64_t kRecordBatches = 1 << 20, kRecordMin = 1 << 19;
 constexpr float kRecordTexels = 0.4f;
 struct BatchRecords {
@@ -52,7 +57,6 @@ struct BatchRecords {
 __host__ __device__ constexpr int record_place(int i) { return 4 * (i & 3) + (i >> 2); }
 
 // br: NULL, or the records; rays without one get the per-batch sums.
-// n_placed then holds the placement counts on entry (launch_count).
 // Texels of a plane that a step crosses at most, of the axis with the fewest.
 float texels_per_step(const SceneDev& sc, float delta);
 hipError_t launch_march_fwd(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
