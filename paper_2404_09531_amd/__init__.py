@@ -452,16 +452,30 @@ def fwd_bwd_l2_records_size(scene: Scene, n: int, n_max: int, delta: float = DEL
     return int(nb)
 
 
+def _spare(nbytes: int, device) -> bool:
+    """Whether nbytes can be had without a failing allocation (which would
+    make the allocator wait for the device and drop its cache) and are at most
+    a quarter of the memory that is free or cached.  Not under graph capture,
+    whose pool would keep them."""
+    if torch.cuda.is_current_stream_capturing():
+        return False
+    free, total = torch.cuda.mem_get_info(device)
+    share = torch.cuda.get_per_process_memory_fraction(device)
+    if free >= 4 * nbytes and share >= 1.0:
+        return True
+    reserved = torch.cuda.memory_reserved(device)
+    if share < 1.0:
+        free = min(free, int(share * total) - reserved)
+    return free >= nbytes and free + reserved - torch.cuda.memory_allocated(device) >= 4 * nbytes
+
+
 def _fwd_bwd_l2_workspace(scene: Scene, n: int, n_max: int, delta: float, t_term: float,
                           nbytes: int) -> torch.Tensor:
     """A workspace for the fused step, with room for the batch records where
-    they help and the device has that much memory left."""
+    they help and the device has that much memory to spare."""
     records = fwd_bwd_l2_records_size(scene, n, n_max, delta, t_term)
-    if records > 0:
-        try:
-            return torch.empty((nbytes + records,), dtype=torch.uint8, device=scene.device)
-        except torch.cuda.OutOfMemoryError:
-            pass
+    if records > 0 and _spare(nbytes + records, scene.device):
+        nbytes += records
     return torch.empty((max(nbytes, 1),), dtype=torch.uint8, device=scene.device)
 
 
@@ -474,7 +488,8 @@ def render_fwd_bwd_l2(scene: Scene, o, d, target, out: Dict[str, torch.Tensor], 
     tensor, or None to skip), and the backward ADDED into float32 `grads`.
     `workspace` is a device uint8 tensor of fwd_bwd_l2_workspace_size bytes;
     one that is larger by fwd_bwd_l2_records_size makes a large batch faster
-    (allocated here if None, with those where the memory is there)."""
+    (allocated here if None, with those where they are at most a quarter of
+    the memory that is free or cached, and never under graph capture)."""
     n = _rays(scene, o, d)
     _need(target, "target", torch.float32, (n, 3))
     for key in ("grid", "plane_xy", "plane_xz", "plane_yz", "mlp"):
