@@ -33,3 +33,18 @@ def test_early_termination_replays(dtype):
         assert s.records > 0  # those of a step without early termination
         assert (om.fwd_bwd_l2_records_size(s.scene, s.n, 256, t_term=t_term) > 0) == (t_term == 0)
         assert written(s, s.need + s.records) == (t_term == 0)
+
+
+@pytest.mark.parametrize("n,zmax", [(66003, 0.25), (66003, 0.02), ((1 << 20) + 3, 0.25)])
+def test_workspace_bounds(n, zmax):
+    """Enough batches, too few (known only on the device), and more than there
+    are records.  The size leaves 256 bytes for the alignment of the part behind
+    the smallest size, so the least workspace that holds the records is shorter."""
+    log(f"test_workspace_bounds: {n} rays, occupied up to {zmax}")
+    s = Step(micro_scene(grid=(20, 18, 9), planes=FINE, m=8, zmax=zmax, seed=5), *oblique(n), n_max=256)
+    least = (s.need + 255) // 256 * 256 + s.records - 256
+    assert s.records > 0 and least <= s.need + s.records
+    assert not written(s, s.need)
+    assert not written(s, least - 1)
+    assert written(s, least)
+    assert written(s, s.need + s.records)
