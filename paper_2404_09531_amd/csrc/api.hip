@@ -709,12 +709,11 @@ int64_t om_sparse_grid_index(const om_scene* scene, int block_shift, int32_t* gr
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = launch_blocks_mark(scene->dev, block_shift, bn[0], bn[1], bn[2], grid_blocks, s);
     // Numbered on the device; only the count comes back, in entry 0 (negated
-    // if that block is kept), which then gets its own id.
+    // if that block is kept), which then gets its own id, before the one wait.
     if (e == hipSuccess) e = launch_blocks_number(grid_blocks, n, s);
     int32_t count = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&count, grid_blocks, sizeof count, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e == hipSuccess) e = launch_blocks_first(grid_blocks, count < 0 ? 1 : 0, s);
+    if (e == hipSuccess) e = launch_blocks_first(grid_blocks, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         hip_status(e, "om_sparse_grid_index");

@@ -271,17 +271,18 @@ __global__ __launch_bounds__(kNumberThreads) void k_blocks_number(int32_t* __res
     if (t == 0) mark[0] = first ? -base : base;
 }
 
-__global__ void k_blocks_first(int32_t* mark, int id) {
-    if (threadIdx.x == 0) mark[0] = id;
+__global__ void k_blocks_first(int32_t* mark) {
+    if (threadIdx.x == 0) mark[0] = mark[0] < 0 ? 1 : 0;
 }
 
 hipError_t launch_blocks_number(int32_t* mark, int64_t n, hipStream_t s) {
-    hipLaunchKernelGGL((uintptr_t)mark & 15u ? k_blocks_number<false> : k_blocks_number<true>, dim3(1), dim3(kNumberThreads), 0, s, mark, n);
+    hipLaunchKernelGGL((uintptr_t)mark & 15u ? k_blocks_number<false> : k_blocks_number<true>, dim3(1),
+                       dim3(kNumberThreads), 0, s, mark, n);
     return hipGetLastError();
 }
 
-hipError_t launch_blocks_first(int32_t* mark, int id, hipStream_t s) {
-    hipLaunchKernelGGL(k_blocks_first, dim3(1), dim3(64), 0, s, mark, id);
+hipError_t launch_blocks_first(int32_t* mark, hipStream_t s) {
+    hipLaunchKernelGGL(k_blocks_first, dim3(1), dim3(64), 0, s, mark);
     return hipGetLastError();
 }
 

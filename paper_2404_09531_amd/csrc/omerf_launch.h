@@ -113,7 +113,7 @@ hipError_t launch_range(const float* x, int64_t n, float* minmax, uint32_t* keys
 hipError_t launch_quantize(const float* x, int64_t n, const float* lo, const float* inv, uint8_t* out, hipStream_t s);
 hipError_t launch_blocks_mark(const SceneDev& sc, int shift, int bnx, int bny, int bnz, int32_t* mark, hipStream_t s);
 hipError_t launch_blocks_number(int32_t* mark, int64_t n, hipStream_t s);
-hipError_t launch_blocks_first(int32_t* mark, int id, hipStream_t s);
+hipError_t launch_blocks_first(int32_t* mark, hipStream_t s);
 hipError_t launch_blocks_fill(const SceneDev& sc, int shift, int bnx, int bny, int bnz, const int32_t* idx,
                               int64_t n_blocks, int units, void* atlas, hipStream_t s);
 hipError_t launch_cast_bf16(const float* src, int64_t n, uint16_t* dst, hipStream_t s);
