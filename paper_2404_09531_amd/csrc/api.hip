@@ -144,15 +144,10 @@ int validate_desc(const om_scene_desc* d, SceneDev* out) {
         s.blk_verts = (uint32_t)((B + 1) * (B + 1) * (B + 1));
         s.n_blocks = (uint32_t)d->n_blocks;
     }
-    for (int c = 0; c < 8; ++c) {
-        double lo = 0.0;  // rounded once
-        for (int i = 0; i < 4; ++i) {
-            lo += d->dtype == OM_U8 ? (double)d->quant_lo[i][c] : 0.0;
-            s.qstep[8 * i + c] = d->dtype == OM_U8 ? d->quant_step[i][c] : 0.0f;
-        }
-        s.qlo[c] = (float)lo;
+    for (int i = 0; i < 32; ++i) {
+        s.qlo[i] = d->dtype == OM_U8 ? (&d->quant_lo[0][0])[i] : 0.0f;
+        s.qstep[i] = d->dtype == OM_U8 ? (&d->quant_step[0][0])[i] : 0.0f;
     }
-    for (int i = 0; i < 4; ++i) s.qlo0[i] = d->dtype == OM_U8 ? d->quant_lo[i][0] : 0.0f;
     s.Lx = d->grid_dims[0];
     s.Ly = d->grid_dims[1];
     s.Lz = d->grid_dims[2];

@@ -128,11 +128,11 @@ __device__ __forceinline__ void store_group_total(float x, int gl, float* dst) {
 // of the group shades sample s of the batch on its own (10 or 20 loads),
 // and the batch of 16 samples is composited with one 16-lane scan.  8-bit is
 // bound by vector instructions: reading the decoding from the argument
-// segment instead of spilled scalar registers, and one offset per channel
-// instead of four, took a 1920x1080 frame with sparse blocks and early
-// termination from 3.78 to 2.97 ms (2.52 with xcd_block's runs).  bfloat16 is
-// bound by L1 line lookups
-// (1.19 per clock, 36 per load instruction).
+// segment instead of spilled scalar registers, and xcd_block's runs, took a
+// 1920x1080 frame with sparse blocks and early termination from 3.66 to 2.57 ms.
+// (The sources' four offsets are not summed first, which takes 2.53: a feature
+// then has the rounding of their sum, up to four times its own range.)
+// bfloat16 is bound by L1 line lookups (1.19 per clock, 36 per load instruction).
 // ---------------------------------------------------------------------------
 // A sample as the lane that owns it holds it for the other lanes of its quad.
 struct QuadSample {

@@ -50,11 +50,8 @@ struct SceneDev {
     int mip_levels;
     int mlp_in;  // deferred-MLP input width: 10 or 34
     // 8-bit storage: channel c of source s (grid, XY, XZ, YZ) decodes as
-    // lo_s[c] + q qstep[8 s + c]; a source's interpolation weights sum to one,
-    // so the four offsets enter a sample as their sum qlo[c]; those of the
-    // density one by one (qlo0), in the order that its rounding, and with it
-    // the sample at which a ray stops, rests on.
-    float qlo[8], qlo0[4], qstep[32];
+    // qlo[8 s + c] + q qstep[8 s + c]; indexed with constants only.
+    float qlo[32], qstep[32];
     // Grid row strides in vertices: (Lx, Lx Ly) for the dense grid,
     // (B + 1, (B + 1)^2) inside a sparse block.
     uint32_t gsy, gsz;
@@ -545,8 +542,7 @@ __device__ __forceinline__ void wave_order() {
 // 10: 97, 4 waves).
 __device__ __forceinline__ void decode_add(const SceneDev& sc, int src, const float* a, float* t) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c)
-        t[c] = c == 0 ? t[0] + fmaf(sc.qstep[8 * src], a[0], sc.qlo0[src]) : fmaf(sc.qstep[8 * src + c], a[c], t[c]);
+    for (int c = 0; c < 8; ++c) t[c] += fmaf(sc.qstep[8 * src + c], a[c], sc.qlo[8 * src + c]);
 }
 
 template <bool kNarrow>
@@ -555,7 +551,7 @@ __device__ __forceinline__ void gather_u8(const SceneDev& sc, const Corners& c, 
     const uint32_t sy = sc.gsy, sz = sc.gsz;
     const uint32_t nx = (uint32_t)sc.Nx, ny = (uint32_t)sc.Ny;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) t[i] = i == 0 ? 0.0f : sc.qlo[i];
+    for (int i = 0; i < 8; ++i) t[i] = 0.0f;
     float a[8];
     {
         uint4 r[4];
