@@ -14,8 +14,8 @@
 // k_tile_list : lists the batches by tile;
 // k_tile_sum  : sums the tiles, each wave over an equal share of the lists.
 //
-// 2^18 rays in float32 (2.5 million batches): keys 0.22 ms, list 0.09, sum
-// 2.63, of which the records' reads at the large copy's rate are about 0.9 and the
+// 2^18 rays in float32 (2.5 million batches): keys 0.26 ms, list 0.09, sum
+// 2.50, of which the records' reads at the large copy's rate are about 0.9 and the
 // rest the four read-add-write steps per batch and plane in LDS, one after
 // another.
 #include "omerf_launch.h"
@@ -116,7 +116,8 @@ __device__ __forceinline__ int block_scan(int x, int* part, int& all) {
     return r;
 }
 
-__global__ __launch_bounds__(kListThreads) void k_tile_scan(int* __restrict__ bins, int nbins, int* __restrict__ total) {
+__global__ __launch_bounds__(kListThreads) void k_tile_scan(int* __restrict__ bins, int nbins,
+                                                            int* __restrict__ total) {
     __shared__ int part[kListThreads];
     const int per = (nbins + kListThreads - 1) / kListThreads;
     const int b0 = min(nbins, (int)threadIdx.x * per), b1 = min(nbins, b0 + per);

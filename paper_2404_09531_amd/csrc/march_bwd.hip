@@ -361,9 +361,10 @@ __global__ __launch_bounds__(kOrderSmallThreads) void k_order_small(const int32_
 // `turns` turns go by its number, further ones by tickets from the counter,
 // `turns` each and requested ahead.  One counter serves a ticket every 40 ns,
 // whatever the waves do in between (a fused step of 4,096 rays took 299 us with
-// two tickets per wave and turn, 211 with none; 16,384 rays 931 and 725), so there are some eight tickets per wave in all,
-// and no more waves than the chip holds: a block that had to wait would start
-// its long first rays last.  The counter is unsigned and ends below 2^32.
+// two tickets per wave and turn, 211 with none; 16,384 rays 931 and 725), so
+// there are some eight tickets per wave in all, and no more waves than the chip
+// holds: a block that had to wait would start its long first rays last.  The
+// counter is unsigned and ends below 2^32.
 template <class Body>
 __device__ __forceinline__ void hand_out(unsigned int* next_ray, int64_t from, int64_t to, int gid, int lane,
                                          Body&& body) {
@@ -391,7 +392,8 @@ __device__ __forceinline__ void hand_out(unsigned int* next_ray, int64_t from, i
 // in flight and 187 so on planes of 256 x 256 texels, 526 and 501 on 2048 x
 // 2048, with everything trained 837 and 761; of 8,192 rays 543 and 516.
 template <class S, bool kSoft, bool kNarrow, bool kFew>
-__global__ __launch_bounds__(kBlock, kFew ? 2 : 4) void k_march_bwd(SceneDev sc, RayParams rp, const float* __restrict__ o_,
+__global__ __launch_bounds__(kBlock, kFew ? 2 : 4) void k_march_bwd(SceneDev sc, RayParams rp,
+                                                       const float* __restrict__ o_,
                                                        const float* __restrict__ d_, int64_t n,
                                                        const int32_t* __restrict__ order, const int* __restrict__ sched,
                                                        unsigned int* __restrict__ next_ray,
@@ -529,11 +531,10 @@ __global__ __launch_bounds__(kBlock, kFew ? 2 : 4) void k_march_bwd(SceneDev sc,
 // next batch's record is loaded while one is scattered.
 //
 // Bound by the scatter's float atomics: 82 million 64-byte requests of 2^18
-// rays in float32 in 4.5 ms, near the 20.6 G/s that they reach beyond L2
-//.  The step took 12.3 ms with
-// the samples replayed and four sources scattered; the rays' order (0.09), their
-// counts (0.18), the forward with records (2.6), this and the tiles' sums (2.9)
-// take 10.4.
+// rays in float32 in 4.5 ms, 88 % of the 20.6 G/s that they reach beyond L2.
+// The step took 12.3 ms with the samples replayed and four sources scattered;
+// the rays' order (0.08), their counts (0.19), the forward with records (2.6),
+// this and the tiles' sums (2.9) take 10.3.
 // ---------------------------------------------------------------------------
 struct RecordLoad {
     float a, v[7], px, py, pz, carry;
@@ -654,8 +655,8 @@ hipError_t launch_march_bwd(const SceneDev& sc, bool bf16, const RayParams& rp, 
     const dim3 block(kBlock);
     const bool soft = rp.occ_inv_eps > 0.0f;
     if (br) {
-        hipLaunchKernelGGL(soft ? k_grad<true> : k_grad<false>, grad_grid, block, 0, s, sc, rp, order, sched, next_ray + 1,
-                           *br, T, n_eval, G8, gV, gxy, gocc);
+        hipLaunchKernelGGL(soft ? k_grad<true> : k_grad<false>, grad_grid, block, 0, s, sc, rp, order, sched,
+                           next_ray + 1, *br, T, n_eval, G8, gV, gxy, gocc);
     }
     typedef void (*Form)(SceneDev, RayParams, const float*, const float*, int64_t, const int32_t*, const int*,
                          unsigned int*, const float*, const int32_t*, const float*, const float*, float*, float*,

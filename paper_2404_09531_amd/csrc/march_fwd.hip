@@ -55,8 +55,8 @@ __global__ __launch_bounds__(kBlock) void k_count(SceneDev sc, RayParams rp, con
 // What a forward leaves for the backward: nothing, the per-batch sums of w v,
 // or a record per batch (the sums for rays without records).  With records,
 // batches of many rays, the rays are taken in the locality order: the forward
-// of 2^18 rays of 16 cameras in float32 2.81 ms as they come and 1.96 so, of
-// 2^20 of 64 in bfloat16 5.27 and 3.63, for 0.05 to 0.15 ms that ordering them
+// of 2^18 rays of 16 cameras in float32 3.31 ms as they come and 2.61 so, of
+// 2^20 of 64 in bfloat16 6.5 and 4.7, for the 0.08 and 0.19 ms that ordering them
 // costs.
 enum { kSaveNone, kSaveSums, kSaveRecords };
 
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kBlock) void k_mark(SceneDev sc, RayParams rp, cons
 
 // ---------------------------------------------------------------------------
 // Forward marches: write F [n][7], T [n], n_placed [n], n_eval [n] (and, with
-// kBW, the per-batch sums of w v).
+// kSaveSums, the per-batch sums of w v, or with kSaveRecords the records).
 // ---------------------------------------------------------------------------
 // Group total of x (inclusive DPP scan; the row's last lane holds it) stored
 // by that lane at dst, for the optional per-batch sums of w v.
@@ -184,7 +184,7 @@ struct GatherBF16 {
 struct GatherBF16Lds {
     static constexpr int kLanes = 4;
     static constexpr int kAhead = 3;                // rows in flight
-    static constexpr int kHalf = 64 * 16 + 16;      // a load, and 16 bytes so that the quad's reads miss each other's banks
+    static constexpr int kHalf = 64 * 16 + 16;      // a load; 16 bytes keep the quad's reads off each other's banks
     static constexpr int kRow = kHalf + 64 * 16;
     static constexpr int kStage = kAhead * kRow;    // with the queues 26,816 bytes per block: six per CU
 
@@ -252,15 +252,14 @@ struct GatherBF16Lds {
 
 // Waves per SIMD the one-lane-per-sample forwards are compiled for: without
 // the soft occupancy and with 32-bit addresses they fit 6 (<= 80 VGPRs)
-// without spilling, with records or two lanes per row 5; the other forms keep
-// the compiler's choice.
-template <class Gather, int kSave, bool kSoft, bool kNarrow>
+// without spilling, with records 5; the other forms keep the compiler's choice.
+template <int kSave, bool kSoft, bool kNarrow>
 constexpr int lane_min_waves() {
     return !kSoft && kNarrow ? (kSave == kSaveRecords ? 5 : 6) : 1;
 }
 
 template <class Gather, int kSave, bool kSoft, bool kSparse, bool kNarrow>
-__global__ __launch_bounds__(kBlock, (lane_min_waves<Gather, kSave, kSoft, kNarrow>())) void k_march_fwd_lane(
+__global__ __launch_bounds__(kBlock, (lane_min_waves<kSave, kSoft, kNarrow>())) void k_march_fwd_lane(
     SceneDev sc, RayParams rp, const float* __restrict__ o_, const float* __restrict__ d_, int64_t n,
     float* __restrict__ F, float* __restrict__ T, int32_t* __restrict__ n_placed, int32_t* __restrict__ n_eval,
     float* __restrict__ BW, BatchRecords br) {
@@ -471,7 +470,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_march_fwd_f32q(
         float col = a;
         col += dpp_row<kRowShr | 4>(col);
         col += dpp_row<kRowShr | 8>(col);
-        const float run1 = carry + row_bcast<12>(col), run2 = run1 + row_bcast<13>(col), run3 = run2 + row_bcast<14>(col);
+        const float run1 = carry + row_bcast<12>(col), run2 = run1 + row_bcast<13>(col);
+        const float run3 = run2 + row_bcast<14>(col);
         const float run = q == 0 ? carry : q == 1 ? run1 : q == 2 ? run2 : run3;
         const float pre = run + dpp_row<kRowShr | 4>(col);
         int nb_eff = nb;

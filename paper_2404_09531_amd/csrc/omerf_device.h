@@ -647,8 +647,8 @@ __device__ __forceinline__ void mlp_input(const float* F7, float3 d, float* x) {
 // pyramid level lv; after two sweeps in a row with no possible sample the level
 // coarsens (when a pyramid is attached), the first possible segment is refined
 // one level at a time, and candidate testing resumes at level 0.
-__device__ __forceinline__ int next_segment(const SceneDev& sc, const RayParams& rp, float3 o, float3 d, int k, int last,
-                                            int gl, int lane) {
+__device__ __forceinline__ int next_segment(const SceneDev& sc, const RayParams& rp, float3 o, float3 d, int k,
+                                            int last, int gl, int lane) {
     int lv = 0, empty_sweeps = 0;
     while (k <= last) {
         const int seg = kGroup << lv;
@@ -704,7 +704,7 @@ __device__ __forceinline__ int count_candidates(const SceneDev& sc, const RayPar
 // ---------------------------------------------------------------------------
 // Candidate driver shared by the forward, placement and backward kernels.
 // ---------------------------------------------------------------------------
-// lattice range of one ray 16 candidates at a time, appends accepted k to
+// Walks the lattice range of one ray 16 candidates at a time, appends accepted k to
 // the group's LDS queue in increasing order and hands full batches (or the
 // final partial batch) to `shade(k, nb)`, which returns true to stop.
 // Lane gl gets the sample at place `pos` of the batch (its own place unless

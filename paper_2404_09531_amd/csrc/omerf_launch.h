@@ -15,6 +15,7 @@ hipError_t launch_place(const SceneDev& sc, const RayParams& rp, const float* o,
                         int32_t* k_out, int32_t* n_placed, hipStream_t s);
 hipError_t launch_mark(const SceneDev& sc, const RayParams& rp, const float* o, const float* d, int64_t n,
                        const int32_t* n_eval, uint8_t* fg, uint8_t* fxy, uint8_t* fxz, uint8_t* fyz, hipStream_t s);
+
 // Batch records of a training step (float32 [slots][kRecFloats]): the forward
 // leaves one per 16-sample batch of a ray, and the backward works from them
 // instead of replaying the samples.
@@ -42,6 +43,16 @@ constexpr int kRecPoint = 8 * kGroup, kRecCarry = 11 * kGroup, kRecFloats = 12 *
 // to 768,000 of 1,116,000 to 966,000 batches evaluated) 5.43 and 5.08, 5.42 and
 // 4.90, 5.26 and 4.66, 4.72 and 4.23 ms; 2^20 of the towers in bfloat16 at 1e-4 /
 // 1e-2 (1,096,000 of 1,892,000, 881,000 of 1,678,000) 6.46 and 6.03, 5.57 and 5.08.
+//
+// The placed batches are known on the device only.  A step that turns out to
+// have fewer than kRecordMin has ordered and counted its rays and runs the
+// kernels' record forms for nothing: 16,500 / 24,000 / 32,000 / 40,000 / 48,000 rays
+// in float32 (169,000 to 490,000 of more than 2^20 batches) 1.69 ms and 1.61 without
+// a workspace for records, 2.15 and 2.09, 2.34 and 2.26, 2.52 and 2.48, 2.76 and
+// 2.71.  Where most rays miss the box it is more, since their keys collide in the
+// locality order (1.1 ms each for its histogram and scatter): 2^20 rays of which 1 %
+// meet it 3.81 and 1.41, none 2.70 and 0.35; with 10 % (1,017,000 batches, records
+// kept) 7.43 and 6.63.
 constexpr int64_t kRecordBatches = 1 << 20, kRecordMin = 1 << 19;
 constexpr float kRecordTexels = 0.4f;
 struct BatchRecords {
@@ -56,9 +67,9 @@ struct BatchRecords {
 // the lane that holds it in the float32 forward.
 __host__ __device__ constexpr int record_place(int i) { return 4 * (i & 3) + (i >> 2); }
 
-// br: NULL, or the records; rays without one get the per-batch sums.
 // Texels of a plane that a step crosses at most, of the axis with the fewest.
 float texels_per_step(const SceneDev& sc, float delta);
+// br: NULL, or the records; rays without one get the per-batch sums.
 hipError_t launch_march_fwd(const SceneDev& sc, int dtype, const RayParams& rp, const float* o, const float* d,
                             int64_t n, float* F, float* T, int32_t* n_placed, int32_t* n_eval, float* batch_wv,
                             const BatchRecords* br, hipStream_t s);
@@ -105,8 +116,8 @@ hipError_t launch_mlp_bwd(const float* W, int mlp_in, const RayParams& rp, const
                           hipStream_t s);
 hipError_t launch_smooth(const float* W, int mlp_in, const float* F, const float* d, int64_t n, const float* perturb,
                          int P, float weight, float* loss, float* dF, float* gmlp, hipStream_t s);
-hipError_t launch_mlp(const float* W, int mlp_in, bool bf16, const RayParams& rp, const float* d, int64_t n, const float* F,
-                      const float* T, const int32_t* n_eval, float* C, hipStream_t s);
+hipError_t launch_mlp(const float* W, int mlp_in, bool bf16, const RayParams& rp, const float* d, int64_t n,
+                      const float* F, const float* T, const int32_t* n_eval, float* C, hipStream_t s);
 hipError_t launch_occ_pyramid(const float2* occ, int Mx, int My, float2* mips, int levels, hipStream_t s);
 hipError_t launch_occ_loss(const float* occ, int64_t cells, float weight, float* loss, float* grad, hipStream_t s);
 hipError_t launch_range(const float* x, int64_t n, float* minmax, uint32_t* keys, hipStream_t s);

@@ -201,8 +201,8 @@ hipError_t launch_order_rays(const float* box_lo, const float* box_hi, const flo
     hipLaunchKernelGGL(k_okey_clear, dim3(blocks_for(kKeyBins)), dim3(kOrderBlock), 0, s, hist);
     hipLaunchKernelGGL(k_okey_hist, dim3(blocks_for(n)), dim3(kOrderBlock), 0, s, o, d, n, kf, keys, hist);
     hipLaunchKernelGGL(k_okey_scan, dim3(1), dim3(kScanThreads), 0, s, hist);
-    hipLaunchKernelGGL(o_out ? k_okey_scatter<true> : k_okey_scatter<false>, dim3(blocks_for(n)), dim3(kOrderBlock), 0, s, o, d, n, keys, hist, order, o_out,
-                       d_out);
+    hipLaunchKernelGGL(o_out ? k_okey_scatter<true> : k_okey_scatter<false>, dim3(blocks_for(n)), dim3(kOrderBlock), 0,
+                       s, o, d, n, keys, hist, order, o_out, d_out);
     return hipGetLastError();
 }
 
