@@ -60,8 +60,8 @@ def parse():
 # The source files each kernel family is compiled from; a committed counter
 # figure is used only while the hash of its family's files is unchanged.
 KERNEL_SOURCES = {
-    "fwd": ("omerf_device.h", "march_fwd.hip"),
-    "bwd": ("omerf_device.h", "bwd_device.h", "march_bwd.hip", "bwd_tiles.hip"),
+    "fwd": ("omerf_device.h", "omerf_launch.h", "march_fwd.hip"),
+    "bwd": ("omerf_device.h", "omerf_launch.h", "bwd_device.h", "march_bwd.hip", "bwd_tiles.hip"),
     "mlp": ("omerf_device.h", "mlp.hip"),
 }
 
@@ -329,7 +329,7 @@ def form_bf16_render(om, torch, t, og, dg, out, kw, n, a, rows, l1_peak, crop_id
     crops["bf16_render"] = outb["C"][crop_idx].double().cpu().numpy()
     return {"Mrays_per_s": round(n / (ms * 1e-3) / 1e6, 2), "ms_per_step": round(ms, 4),
             "march_ms": round(mb_ms, 4), "mlp_ms": round(lb_ms, 4),
-            "roofline": hbm_roofline("k_march_fwd_lane<GatherBF16>", "oblique-1080p", mb_ms,
+            "roofline": hbm_roofline("k_march_fwd_lane<GatherBF16Lds>", "oblique-1080p", mb_ms,
                                      sum(rows.values()) * 16 + n * 64, sb * 320 + n * 64, l1_peak),
             "psnr_vs_fp32_render_db": _psnr(outb["C"].cpu().numpy(), out["C"].cpu().numpy()),
             "max_abs_vs_fp32_render": float((outb["C"] - out["C"]).abs().max().item())}
@@ -472,8 +472,9 @@ def form_fp32_fwd_bwd(om, scenegen, torch, scene, t, kw, a, occ_eps=0.0):
            "samples_per_ray": round(s2 / n2, 1), "targets": "forward colours + N(0, 0.05), seeded",
            "bwd_Msamples_per_s": round(s2 / (b_ms * 1e-3) / 1e6, 1)}
     if occ_eps == 0:
-        res["roofline"] = _train_rooflines(om, torch, scene, o2g, d2g, out2, kw, f_ms, b_ms, "k_march_fwd_f32q<true>",
-                                           ("k_mlp_bwd<10>", "k_march_bwd<F32Store>"), "train-2^18", 32)
+        res["roofline"] = _train_rooflines(om, torch, scene, o2g, d2g, out2, kw, f_ms, b_ms,
+                                           "k_march_fwd_f32q<kSaveSums>", ("k_mlp_bwd<10>", "k_march_bwd<F32Store>"),
+                                           "train-2^18", 32)
     return res
 
 
@@ -657,7 +658,7 @@ def form_towers(om, scenegen, torch, a, ordered=False):
             "Mrays_per_s": round(n / (ms * 1e-3) / 1e6, 3), "ms_per_step": round(ms, 3),
             "fwd_ms": round(f_ms, 3), "bwd_ms": round(b_ms, 3), "bwd_Msamples_per_s": round(se / (b_ms * 1e-3) / 1e6, 1),
             "roofline": _train_rooflines(om, torch, scene_b, og, dg, out, kw, f_ms, b_ms,
-                                         "k_march_fwd_lane<GatherBF16,kBW>", ("k_mlp_bwd<10>", "k_march_bwd<BF16Store>"),
+                                         "k_march_fwd_lane<GatherBF16,kSaveSums>", ("k_mlp_bwd<10>", "k_march_bwd<BF16Store>"),
                                          "towers-2^20", 16),
             "samples_per_ray": round(float(npl.mean()), 1), "max_samples": int(npl.max()),
             "n_placed_hist_bins32": hist.tolist(), "n_eval_hist_bins32": hist_eval.tolist()}
@@ -809,11 +810,12 @@ def main():
     #   ray returned to registers, against the calibrated cache-resident rate.
     rows = rows_read(om, scene, og, dg, n_max, out["n_eval"])
     l1_quad = l1_gather_peak(torch, 4)
+    l1_pair = l1_gather_peak(torch, 2)  # bfloat16 renders: two lanes per corner pair
     l1_lane = l1_gather_peak(torch, 1)
-    roofline = hbm_roofline("k_march_fwd_f32q<false>", "oblique-1080p", march_ms, sum(rows.values()) * 32 + n * 64,
+    roofline = hbm_roofline("k_march_fwd_f32q<kSaveNone>", "oblique-1080p", march_ms, sum(rows.values()) * 32 + n * 64,
                             samples * 640 + n * 64, l1_quad)
     roofline["rows_read"] = rows
-    print(f"[bench] rows read {rows}, gather calibration {l1_quad['GBps']} / {l1_lane['GBps']} GB/s",
+    print(f"[bench] rows read {rows}, gather calibration {l1_quad['GBps']} / {l1_pair['GBps']} / {l1_lane['GBps']} GB/s",
           file=sys.stderr, flush=True)
 
     w, h = recipe["width"], recipe["height"]
@@ -834,7 +836,7 @@ def main():
     if "fp32_render_row_order_ordered" in want:
         forms["fp32_render_row_order_ordered"] = form_row_order_ordered(om, scenegen, torch, scene, kw, a)
     if "bf16_render" in want:
-        forms["bf16_render"] = form_bf16_render(om, torch, t, og, dg, out, kw, n, a, rows, l1_lane, crop_idx, crops)
+        forms["bf16_render"] = form_bf16_render(om, torch, t, og, dg, out, kw, n, a, rows, l1_pair, crop_idx, crops)
     if "fp32_render_ert" in want:
         forms["fp32_render_ert"] = form_fp32_render_ert(om, torch, scene, og, dg, out, kw, n, a)
     if "sparse_render" in want:
@@ -850,7 +852,7 @@ def main():
     if "fp32_fwd_bwd_enc_smooth" in want:
         forms["fp32_fwd_bwd_enc_smooth"] = form_fp32_enc_smooth(om, scenegen, torch, t, kw, a)
     if "bf16_render_4k_x8" in want:
-        forms["bf16_render_4k_x8"] = form_bf16_4k(om, scenegen, torch, t, kw, a, l1_lane, crops)
+        forms["bf16_render_4k_x8"] = form_bf16_4k(om, scenegen, torch, t, kw, a, l1_pair, crops)
     if "high_altitude_mips" in want:
         forms["high_altitude_mips"] = form_high_altitude(om, scenegen, torch, t, a)
     if "towers_bf16_fwd_bwd" in want:

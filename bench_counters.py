@@ -21,8 +21,8 @@ recursively for ``*_counter_collection.csv`` / ``*_kernel_stats.csv``):
     python bench_counters.py stats --dir DIR
 
 ``KEY=PATTERN``: KEY is the kernel key bench.py looks up (e.g.
-``k_march_fwd_lane<GatherBF16>``), PATTERN a substring of the demangled
-kernel name (e.g. ``k_march_fwd_lane<omerf::GatherBF16, false, false, false>``).
+``k_march_fwd_lane<GatherBF16Lds>``), PATTERN a substring of the demangled
+kernel name (e.g. ``k_march_fwd_lane<omerf::GatherBF16Lds, 0, false, false, true>``).
 
 HBM bytes: FETCH_SIZE and WRITE_SIZE (KiB per dispatch) each scaled by what
 the same counter reads for a device-to-device copy of 1 GiB in the same
@@ -88,7 +88,7 @@ def source_hash(family: str) -> str:
 
 
 def family_of(key: str) -> str:
-    if key.startswith("k_march_bwd"):
+    if key.startswith(("k_march_bwd", "k_grad", "k_tile", "k_order")):
         return "bwd"
     if key.startswith("k_mlp"):
         return "mlp"

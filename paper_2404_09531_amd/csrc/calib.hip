@@ -8,7 +8,7 @@
 // feature rows are re-read from L1/L2 many times per frame.  This kernel
 // measures that rate with the same load shape on data that is resident in
 // each CU's L1: every lane issues 16-byte loads, lanes in groups of `span`
-// (1, 4 or 16) read one contiguous span of span x 16 bytes, and each group
+// (1 to 16) read one contiguous span of span x 16 bytes, and each group
 // picks its span with its own linear congruential sequence inside a small
 // buffer, so the lanes of one load instruction touch up to 64 / span
 // different places, as the gathers do.  Bytes returned = loads x 16.

@@ -530,8 +530,8 @@ __global__ __launch_bounds__(kBlock, kFew ? 2 : 4) void k_march_bwd(SceneDev sc,
 // YZ sums by tiles (bwd_tiles.hip); the grid and XY are scattered here.  The
 // next batch's record is loaded while one is scattered.
 //
-// Bound by the scatter's float atomics: 82 million 64-byte requests of 2^18
-// rays in float32 in 4.5 ms, 88 % of the 20.6 G/s that they reach beyond L2.
+// Bound by the scatter's float atomics: 83 million 64-byte requests of 2^18
+// rays in float32 in 4.5 ms, 89 % of the 20.6 G/s that they reach beyond L2.
 // The step took 12.3 ms with the samples replayed and four sources scattered;
 // the rays' order (0.08), their counts (0.19), the forward with records (2.6),
 // this and the tiles' sums (2.9) take 10.3.
